@@ -157,7 +157,13 @@ typedef struct cfr_options {
     void *workspace;        /* device memory of >= cfr_workspace_size bytes,
                                or NULL to let the library allocate it       */
     size_t workspace_bytes;
-    int use_graph;          /* 1: replay a captured HIP graph per iteration  */
+    int use_graph;          /* 1: replay a captured HIP graph per iteration, or,
+                               for games whose iteration state fits the LDS of
+                               the compute units, run whole iterations inside
+                               one launch (set up once enough iterations have
+                               been asked for to repay it; it keeps a copy of
+                               the payoff streams outside any caller workspace;
+                               same results bit for bit); 0: a launch per step  */
     int spmv_order;         /* CFR_SPMV_*                                    */
     int down_pass;          /* CFR_DOWN_*                                    */
     int up_pass;            /* CFR_UP_*                                      */

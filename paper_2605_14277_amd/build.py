@@ -22,8 +22,9 @@ INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(PKG, "libcfr.so")
 LIB_ASAN = os.path.join(PKG, "libcfr_asan.so")
 OBJ = os.path.join(ROOT, "_build")
-SOURCES = ["cfr_api.hip", "cfr_engine.hip", "cfr_kernels.hip"]
-HOST_SOURCES = ["cfr_api.hip", "cfr_engine.hip"]  # no kernels in these
+SOURCES = ["cfr_api.hip", "cfr_engine.hip", "cfr_resident_plan.hip", "cfr_kernels.hip",
+           "cfr_resident.hip"]
+HOST_SOURCES = ["cfr_api.hip", "cfr_engine.hip", "cfr_resident_plan.hip"]  # no kernels in these
 
 COMMON = ["--offload-arch=gfx950", "-std=c++17", "-fPIC",
           # sums are taken in a fixed order without contraction, so the FP64
@@ -81,7 +82,8 @@ def build(verbose: bool = False, asan: bool = True) -> str:
         tmp = LIB_ASAN + ".tmp"
         _run_all([[cc, "--offload-arch=gfx950", "-shared", "-fPIC", "-shared-libasan",
                    "-Xarch_host", "-fsanitize=address",
-                   *[obj_asan[s] for s in HOST_SOURCES], obj["cfr_kernels.hip"], "-o", tmp]],
+                   *[obj_asan[s] for s in HOST_SOURCES],
+                   *[obj[s] for s in SOURCES if s not in HOST_SOURCES], "-o", tmp]],
                  verbose)
         os.replace(tmp, LIB_ASAN)
     return LIB

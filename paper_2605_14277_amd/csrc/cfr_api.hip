@@ -732,7 +732,11 @@ int cfr_get_state(cfr_solver *s, void *out, size_t len)
         }
     }
     if (err != hipSuccess) return e.device_error("state copy", err);
-    return e.sync("state copy");
+    const int rc = e.sync("state copy");
+    if (rc) return rc;
+    cfr::Scalars hs;
+    std::memcpy(&hs, (const char *)out + sizeof h, sizeof hs);
+    return e.check_mark(hs);
 }
 
 int cfr_set_state(cfr_solver *s, const void *in, size_t len)

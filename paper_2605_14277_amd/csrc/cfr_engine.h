@@ -15,6 +15,7 @@
 
 #include "cfr.h"
 #include "cfr_internal.h"
+#include "cfr_resident.h"
 
 namespace cfr {
 
@@ -206,6 +207,12 @@ struct Slot {
     std::vector<int32_t> qptr[2];        // its local quad row pointers
     std::vector<int32_t> old_of_new[2];  // internal -> caller numbering
     std::vector<SpmvBlock> blocks[2];    // product blocks (global fields)
+    // the resident loop: the treeplexes it is planned from (null when the
+    // game has too many sequences for it), and the plan for the current
+    // tiling (null: not made, or none fits)
+    std::shared_ptr<ResSource> res_src;
+    std::shared_ptr<ResidentPlan> res;
+    int res_tried = 0;  // most workgroups a plan was sought for
     double last[5] = {0, 0, 0, 0, 0};    // last evaluation: expl, NashConv, BR1, BR2, value
     // asynchronous admission: host copies the uploads read, and the event
     // that marks their completion on the upload stream
@@ -325,6 +332,20 @@ struct Engine {
     double host_s[kHostN] = {0, 0, 0, 0, 0, 0, 0};
     int64_t host_n[kHostN] = {0, 0, 0, 0, 0, 0, 0};
 
+    // The resident loop over the iterating games: -1 not decided since their
+    // set or tiling changed, 0 not used, 1 its teams are set up.
+    int resident = -1;
+    bool res_ran = false;  // some launch of it was enqueued (its failure mark is read back)
+    char *res_dev = nullptr;  // teams and workgroup map
+    size_t res_dev_bytes = 0;
+    ResTeam *res_teams = nullptr;
+    int32_t *res_map = nullptr;
+    int res_grid = 0;
+    uint32_t res_lds = 0;
+    int res_threads = 0;
+    double res_asked = 0;  // iterations asked for while the loop was not set up
+    bool res_coop = false;
+
     // per-launch timing of the payoff products (HIP events on st)
     bool timing = false;
     std::vector<std::pair<hipEvent_t, hipEvent_t>> events[2];
@@ -390,6 +411,13 @@ struct Engine {
     hipError_t build_graph();
     // n iterations of every active game (no checks).
     int iterate(int64_t n);
+    // Decides on the resident loop for the iterating games and sets up its
+    // teams (plans are kept with the games).
+    int setup_resident(const std::vector<int> &act);
+    int build_resident(int slot, int max_blocks);
+    void drop_resident(Slot &s);
+    // The failure mark of a game's scalars, as copied back.
+    int check_mark(const Scalars &h);
     // Evaluates the average (or current) profile of the games in `set`;
     // results land in each slot's `last`.
     int evaluate(const std::vector<int> &set, int kind);
@@ -397,7 +425,7 @@ struct Engine {
     // scalars to `out` (host memory of slots.size() records) on the stream;
     // then, once that copy has completed, the set's results from `out`.
     int evaluate_launch(const std::vector<int> &set, int kind, Scalars *out);
-    void evaluate_collect(const std::vector<int> &set, const Scalars *out);
+    int evaluate_collect(const std::vector<int> &set, const Scalars *out);
     // After a check of `set`: games that met their stopping rule stop.
     void apply_check(const std::vector<int> &set);
     // n iterations with checks every check_every iterations; games that meet

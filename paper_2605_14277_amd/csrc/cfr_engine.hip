@@ -1042,6 +1042,10 @@ void Engine::release()
     pending = false;
     if (own_ws && ws) (void)hipFree(ws);
     ws = nullptr;
+    for (Slot &s : slots) drop_resident(s);
+    if (res_dev) (void)hipFree(res_dev);
+    res_dev = nullptr;
+    res_dev_bytes = 0;
     for (QuadStore &Q : quad) {
         if (Q.ptr) (void)hipFree(Q.ptr);
         if (Q.idx) (void)hipFree(Q.idx);
@@ -1105,6 +1109,7 @@ void Engine::drop_quads(Slot &s, int which)
     s.qptr[which].clear();
     s.qptr[which].shrink_to_fit();
     if (vec[which] == 3) s.blocks[which].clear();
+    drop_resident(s);
 }
 
 int Engine::grow_quads(int which, int64_t need)
@@ -1276,13 +1281,23 @@ int Engine::set_perm(int which, int on)
     return CFR_OK;
 }
 
+void Engine::drop_resident(Slot &s)
+{
+    s.res.reset();
+    s.res_tried = 0;
+    resident = -1;
+}
+
 void Engine::repartition(int which, int items_, int rows_, int vec_)
 {
     items[which] = items_;
     rows[which] = rows_;
     vec[which] = vec_;
     for (Slot &s : slots)
-        if (s.live) partition(s, which);
+        if (s.live) {
+            partition(s, which);
+            drop_resident(s);
+        }
     it.valid = false;
     ev.valid = false;
     drop_graph();
@@ -1437,6 +1452,22 @@ int Engine::add(const HostGame &hg, const GameImage &img, const GameParams &gp, 
             s.fuse_blocks[p] = pl.fuse_blocks;
             s.fuse_off[p] = pl.fuse_off;
             s.fuse_list[p] = pl.fuse_list;
+        }
+    }
+    // the treeplexes for the resident loop, where its state can fit
+    if (!no_alloc && !async && (int64_t)hg.pl[0].n_seq + hg.pl[1].n_seq <= kResSeqMax) {
+        s.res_src = std::make_shared<ResSource>();
+        for (int p = 0; p < 2; ++p) {
+            const PlayerPlan &pl = hg.pl[p];
+            ResSource &rs = *s.res_src;
+            rs.inf_first[p] = pl.inf_first;
+            rs.inf_par[p].resize((size_t)pl.n_inf);
+            for (int32_t j = 0; j < pl.n_inf; ++j)
+                rs.inf_par[p][(size_t)j] = pl.seq_par[(size_t)pl.inf_first[(size_t)j]];
+            rs.child_ptr[p] = pl.child_ptr;
+            rs.child_idx[p] = pl.child_idx;
+            rs.lvl_inf[p] = pl.lvl_inf;
+            rs.lvl_seq[p] = pl.lvl_seq;
         }
     }
     // payoff matrix: row pointers at the row player's sequences, indices
@@ -1778,6 +1809,7 @@ int Engine::build_tables(Tables &T, char *region, const std::vector<int> &set)
 int Engine::rebuild()
 {
     drop_graph();
+    resident = -1;
     const std::vector<int> act = active_set();
     hipError_t e = wait_uploads(act);
     if (e != hipSuccess) return device_error("admission copies", e);
@@ -1996,6 +2028,237 @@ hipError_t Engine::build_graph()
     return hipGraphInstantiate(&gexec, graph, nullptr, nullptr, 0);
 }
 
+// Device memory that frees itself with its last owner.
+static std::shared_ptr<char> device_buffer(size_t bytes)
+{
+    void *p = nullptr;
+    if (hipMalloc(&p, bytes) != hipSuccess) {
+        (void)hipGetLastError();
+        return nullptr;
+    }
+    return std::shared_ptr<char>((char *)p, [](char *q) { (void)hipFree(q); });
+}
+
+int Engine::build_resident(int k, int max_blocks)
+{
+    Slot &s = slots[(size_t)k];
+    s.res_tried = max_blocks;
+    s.res.reset();
+    auto plan = std::make_shared<ResidentPlan>();
+    ResTeam &T = plan->team;
+    T = ResTeam{};
+    ResRows rows[2];
+    for (int w = 0; w < 2; ++w) {
+        const bool quads = vec[w] == 3 && !sequential();
+        T.quads[w] = quads ? 1 : 0;
+        rows[w].ptr = quads ? &s.qptr[w] : &s.ptr[w];
+        rows[w].lr.assign((size_t)s.n_seq[w], 0);
+        for (const SpmvBlock &b : s.blocks[w]) {
+            // a row longer than a block is summed by a tree over a block
+            if (b.n > spmv_block_cap_v(items[w], vec[w])) return CFR_OK;
+            if (sequential()) continue;
+            // the lanes k_spmv gives each row of this block
+            int lanes = 64, lr = 6;
+            while (lanes > 1 && lanes * b.nr > kSpmvThreads) lanes >>= 1, --lr;
+            while (lanes > 1 && lanes > 2 * (b.n / b.nr + 1)) lanes >>= 1, --lr;
+            for (int32_t r = 0; r < b.nr; ++r)
+                rows[w].lr[(size_t)(b.row0 - s.sb[w] + r)] = (uint8_t)lr;
+        }
+    }
+    if (!plan_resident(*s.res_src, rows, s.sb, prec, max_blocks, *plan)) return CFR_OK;
+    const size_t V = value_bytes(prec), C = compute_bytes(prec);
+    size_t at = 0;
+    auto take = [&at](size_t bytes) {
+        const size_t a = at;
+        at = (at + bytes + 255) & ~(size_t)255;
+        return a;
+    };
+    // host-written part first, then the streams and the exchange arrays
+    const size_t o_part = take(plan->part.size() * sizeof(ResPart)), o_i32 = take(4 * plan->i32.size()),
+                 o_u16 = take(2 * plan->u16.size()), o_chunk = take(plan->chunk.size() * sizeof(ResChunk)),
+                 o_row = take(4 * plan->row.size()), o_src = take(4 * plan->src.size()),
+                 o_local[2] = {take(4 * plan->local[0].size()), take(4 * plan->local[1].size())};
+    const size_t host_bytes = at;
+    size_t o_idx[2], o_val[2], o_cut[2], o_gx[2];
+    for (int w = 0; w < 2; ++w) {
+        o_idx[w] = take(4 * (size_t)std::max<int64_t>(plan->elements[w], 1));
+        o_val[w] = take((T.quads[w] ? 4 : 1) * V * (size_t)std::max<int64_t>(plan->elements[w], 1));
+    }
+    const size_t zero0 = at;
+    for (int p = 0; p < 2; ++p) {
+        o_cut[p] = take(C * (size_t)std::max(plan->sh[p].ncut, 1));
+        o_gx[p] = take(V * (size_t)std::max(plan->sh[p].nq, 1));
+    }
+    const size_t o_bar = take(4 * (size_t)kResBarWords);
+    plan->dev = device_buffer(at);
+    if (!plan->dev) return CFR_OK;  // the launch-per-step path needs no copy
+    char *D = plan->dev.get();
+    std::vector<char> h(host_bytes, 0);
+    auto put = [&h](size_t o, const void *src, size_t bytes) {
+        if (bytes) std::memcpy(h.data() + o, src, bytes);
+    };
+    put(o_part, plan->part.data(), plan->part.size() * sizeof(ResPart));
+    put(o_i32, plan->i32.data(), 4 * plan->i32.size());
+    put(o_u16, plan->u16.data(), 2 * plan->u16.size());
+    put(o_chunk, plan->chunk.data(), plan->chunk.size() * sizeof(ResChunk));
+    put(o_row, plan->row.data(), 4 * plan->row.size());
+    put(o_src, plan->src.data(), 4 * plan->src.size());
+    for (int p = 0; p < 2; ++p)
+        put(o_local[p], plan->local[p].data(), 4 * plan->local[p].size());
+    T.slot = k;
+    T.blocks = plan->blocks;
+    T.part = (const ResPart *)(D + o_part);
+    T.i32 = (const int32_t *)(D + o_i32);
+    T.u16 = (const uint16_t *)(D + o_u16);
+    T.chunk = (const ResChunk *)(D + o_chunk);
+    T.row = (const uint32_t *)(D + o_row);
+    T.bar = (uint32_t *)(D + o_bar);
+    for (int p = 0; p < 2; ++p) {
+        T.sh[p] = plan->sh[p];
+        T.seq0[p] = (int32_t)s.sb[p];
+        T.idx[p] = (const int32_t *)(D + o_idx[p]);
+        T.val[p] = D + o_val[p];
+        T.cutv[p] = D + o_cut[p];
+        T.gx[p] = D + o_gx[p];
+        const int w = 1 - p;  // the product that gathers player p's strategy
+        T.pub[p] = plan->blocks > 1 || T.quads[w] ? (perm_on[w] ? 2 : 1) : 0;
+    }
+    hipError_t e = hipMemcpyAsync(D, h.data(), host_bytes, hipMemcpyHostToDevice, st);
+    if (e == hipSuccess) e = hipMemsetAsync(D + zero0, 0, at - zero0, st);
+    for (int w = 0; w < 2 && e == hipSuccess; ++w) {
+        const int p = 1 - w;
+        const bool quads = T.quads[w] != 0;
+        e = launch_res_fill(prec, quads, plan->n_chunk[w], T.chunk + plan->chunk0[w], T.row,
+                            (const int32_t *)(D + o_src),
+                            quads ? (const int32_t *)quad[w].idx : idx[w],
+                            quads ? quad[w].val : val[w], quads ? s.qb[w] : s.nb,
+                            perm_on[w] ? dp[p].perm : nullptr,
+                            T.pub[p] == 0 ? (const int32_t *)(D + o_local[p]) : nullptr,
+                            (int32_t)s.sb[p], (int32_t *)(D + o_idx[w]),
+                            D + o_val[w], st);
+    }
+    if (e == hipSuccess) e = hipStreamSynchronize(st);
+    if (e != hipSuccess) return device_error("resident loop set-up", e);
+    // only the device copies are read from here on
+    plan->part = {};
+    plan->i32 = {};
+    plan->u16 = {};
+    plan->chunk = {};
+    plan->row = {};
+    plan->src = {};
+    plan->local[0] = plan->local[1] = {};
+    plan->n_seq = s.n_seq[0] + s.n_seq[1];
+    s.res = plan;
+    return CFR_OK;
+}
+
+int Engine::setup_resident(const std::vector<int> &act)
+{
+    resident = 0;
+    if (no_alloc || !use_graph || async_admission || down_pass != CFR_DOWN_DEFAULT ||
+        up_pass != CFR_UP_DEFAULT || act.empty() || act.size() > (size_t)kResTeamsMax)
+        return CFR_OK;
+    // a workgroup's LDS holds some 2,500 sequences
+    auto need = [&](const Slot &s) { return (s.n_seq[0] + s.n_seq[1]) / 2500 + 1; };
+    auto load = [&](const Slot &s) { return (double)s.nnz + 8.0 * (s.n_seq[0] + s.n_seq[1]); };
+    double total = 0;
+    int64_t spare = kResCus;
+    for (int k : act) {
+        const Slot &s = slots[(size_t)k];
+        if (!s.res_src || std::max(s.n_levels[0], s.n_levels[1]) > kDownAllMaxDepth) return CFR_OK;
+        total += load(s);
+        spare -= need(s);
+    }
+    spare = std::max<int64_t>(spare, 0);
+    HostTimer timer(&host_s[kHostTables], &host_n[kHostTables]);
+    // each game's share of the compute units; plans made for another set are
+    // kept while all teams fit
+    for (int attempt = 0; attempt < 2; ++attempt) {
+        int64_t blocks = 0;
+        bool many = false;
+        for (int k : act) {
+            Slot &s = slots[(size_t)k];
+            const int most = act.size() == 1
+                                 ? kResCus
+                                 : (int)(need(s) + load(s) / total * (double)spare);
+            if (s.res_tried == 0 || (attempt && s.res_tried != most)) {
+                int rc = build_resident(k, most);
+                if (rc) return rc;
+            }
+            if (!s.res) return CFR_OK;
+            if (act.size() == 1) {
+                // the launches of a game alone: about 36 us for the chain,
+                // its streams at 5 TB/s and its sweeps' bytes at 4 TB/s
+                double us = 36.0 + (s.n_seq[0] + s.n_seq[1]) * 60.0 / 4e6;
+                for (int w = 0; w < 2; ++w) us += it.bytes[w] / 5e6;
+                if (s.res->cost_us > us) return CFR_OK;
+            }
+            blocks += s.res->blocks;
+            many = many || s.res->blocks > 1;
+        }
+        // teams with barriers have to be resident all together, one
+        // workgroup per compute unit
+        if (many && blocks > kResCus) continue;
+        // workgroup i runs on XCD i % 8: teams of at most 32 on one XCD
+        std::vector<int> order(act);
+        std::stable_sort(order.begin(), order.end(), [&](int a, int b) {
+            return slots[(size_t)a].res->blocks > slots[(size_t)b].res->blocks;
+        });
+        std::vector<ResTeam> teams;
+        std::vector<int32_t> lane[kResXcds];
+        res_lds = 0;
+        res_threads = many ? kResThreadsMax : 256;
+        for (int k : order) {
+            const ResidentPlan &pl = *slots[(size_t)k].res;
+            const int32_t t = (int32_t)teams.size();
+            teams.push_back(pl.team);
+            res_lds = std::max(res_lds, pl.lds);
+            if (pl.n_seq > kResFewSeq) res_threads = kResThreadsMax;
+            int x = 0;
+            for (int i = 1; i < kResXcds; ++i)
+                if (lane[i].size() < lane[x].size()) x = i;
+            const bool one = pl.blocks <= kResXcdCus &&
+                             (!many || lane[x].size() + (size_t)pl.blocks <= (size_t)kResXcdCus);
+            for (int32_t r = 0; r < pl.blocks; ++r) {
+                if (!one && r > 0)
+                    for (int i = x = 0; i < kResXcds; ++i)
+                        if (lane[i].size() < lane[x].size()) x = i;
+                lane[x].push_back(t | r << 16);
+            }
+        }
+        size_t depth = 0;
+        for (auto &l : lane) depth = std::max(depth, l.size());
+        std::vector<int32_t> map(depth * kResXcds, -1);
+        for (int x = 0; x < kResXcds; ++x)
+            for (size_t i = 0; i < lane[x].size(); ++i) map[i * kResXcds + (size_t)x] = lane[x][i];
+        const size_t tb = (teams.size() * sizeof(ResTeam) + 255) & ~(size_t)255;
+        const size_t need = tb + 4 * map.size();
+        if (need > res_dev_bytes) {
+            if (res_dev) (void)hipFree(res_dev);
+            res_dev = nullptr;
+            res_dev_bytes = 0;
+            void *p = nullptr;
+            if (hipMalloc(&p, need) != hipSuccess) {
+                (void)hipGetLastError();
+                return CFR_OK;
+            }
+            res_dev = (char *)p;
+            res_dev_bytes = need;
+        }
+        res_teams = (ResTeam *)res_dev;
+        res_map = (int32_t *)(res_dev + tb);
+        hipError_t e = h2d(res_teams, teams.data(), teams.size(), st);
+        if (e == hipSuccess) e = h2d(res_map, map.data(), map.size(), st);
+        if (e == hipSuccess) e = hipStreamSynchronize(st);
+        if (e != hipSuccess) return device_error("resident loop set-up", e);
+        res_grid = (int)map.size();
+        res_coop = many;
+        resident = 1;
+        return CFR_OK;
+    }
+    return CFR_OK;
+}
+
 int Engine::iterate(int64_t n)
 {
     if (n <= 0) return CFR_OK;
@@ -2011,6 +2274,36 @@ int Engine::iterate(int64_t n)
         if (slots[(size_t)k].gp.variant < CFR_VANILLA)
             return fail(CFR_ESTATE, "a game has no regret minimiser set");
     hipError_t e = hipSuccess;
+    if (n >= kResMinIterations) {
+        if (resident < 0) {
+            // planning, the streams' copy and their memory are paid once: by
+            // as many iterations as they save
+            res_asked += (double)n;
+            double save = 0, cost = 0;
+            for (int k : act) {
+                const Slot &s = slots[(size_t)k];
+                save += kResSaveUs / (double)act.size();
+                cost += s.res ? 0.0 : kResSetupUs + kResSetupSeqUs * (s.n_seq[0] + s.n_seq[1]);
+            }
+            if (res_asked * save >= cost) {
+                int rc = setup_resident(act);
+                if (rc) return rc;
+            }
+        }
+        hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+        if (resident == 1 && !timing &&
+            hipStreamIsCapturing(st, &cs) == hipSuccess && cs == hipStreamCaptureStatusNone) {
+            HostTimer timer(&host_s[kHostEnqueue], &host_n[kHostEnqueue]);
+            for (int64_t i = 0; i < n && e == hipSuccess; i += kResLaunchIterations)
+                e = launch_resident(prec, res_teams, res_map, res_grid, res_lds, res_threads, res_coop,
+                                    (int)std::min<int64_t>(kResLaunchIterations, n - i), mode, sc,
+                                    dp[0], dp[1], st);
+            if (e != hipSuccess) return device_error("iteration launch", e);
+            res_ran = true;
+            for (int k : act) slots[(size_t)k].t += n;
+            return CFR_OK;
+        }
+    }
     // Capturing and instantiating the iteration's graph costs about as much
     // host time as launching twenty iterations directly.  A batch's set of
     // games often changes at every check, so the first short run after a
@@ -2086,11 +2379,13 @@ int Engine::evaluate_launch(const std::vector<int> &set, int kind, Scalars *out)
     return CFR_OK;
 }
 
-void Engine::evaluate_collect(const std::vector<int> &set, const Scalars *out)
+int Engine::evaluate_collect(const std::vector<int> &set, const Scalars *out)
 {
     reap_uploads(false);
     for (int k : set) {
         Slot &s = slots[(size_t)k];
+        const int rc = check_mark(out[(size_t)k]);
+        if (rc) return rc;
         const double br1 = out[(size_t)k].out[0], br2 = out[(size_t)k].out[1];
         s.last[0] = (br1 + br2) / 2.0;
         s.last[1] = br1 + br2;
@@ -2099,6 +2394,14 @@ void Engine::evaluate_collect(const std::vector<int> &set, const Scalars *out)
         s.last[4] = out[(size_t)k].out[2];
         s.last_t = s.t;
     }
+    return CFR_OK;
+}
+
+int Engine::check_mark(const Scalars &h)
+{
+    if (!h.pad[0]) return CFR_OK;
+    failed = true;
+    return fail(CFR_EDEVICE, "the workgroups of an iteration launch lost each other");
 }
 
 int Engine::evaluate(const std::vector<int> &set, int kind)
@@ -2110,8 +2413,7 @@ int Engine::evaluate(const std::vector<int> &set, int kind)
     if (rc) return rc;
     rc = sync("evaluation");
     if (rc) return rc;
-    evaluate_collect(set, h.data());
-    return CFR_OK;
+    return evaluate_collect(set, h.data());
 }
 
 void Engine::apply_check(const std::vector<int> &set)
@@ -2215,7 +2517,8 @@ int Engine::run_end()
     pending = false;
     hipError_t e = hipEventSynchronize(eval_ev);
     if (e != hipSuccess) return device_error("check period", e);
-    evaluate_collect(pending_set, eval_stage);
+    const int rc = evaluate_collect(pending_set, eval_stage);
+    if (rc) return rc;
     apply_check(pending_set);
     pending_set.clear();
     return CFR_OK;
@@ -2263,10 +2566,11 @@ int Engine::fetch_vector(int k, int player, int what, std::vector<double> &out)
     if (e != hipSuccess) return device_error("admission copies", e);
     e = hipMemcpyAsync(h.data(), (const char *)src + el * (size_t)S, n * el,
                                   hipMemcpyDeviceToHost, st);
-    if (e == hipSuccess && what == 1)
+    if (e == hipSuccess && (what == 1 || res_ran))
         e = hipMemcpyAsync(&hs, sc + k, sizeof hs, hipMemcpyDeviceToHost, st);
     if (e != hipSuccess) return device_error("device-to-host copy", e);
     int rc = sync("device-to-host copy");
+    if (!rc) rc = check_mark(hs);
     if (rc) return rc;
     auto load = [&](size_t i) -> double {
         if (el == 8) {
