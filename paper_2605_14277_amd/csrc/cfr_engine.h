@@ -179,6 +179,13 @@ struct QuadStore {
     void *val = nullptr;      // [4 * cap] value type
     int64_t cap = 0;
     RangeAlloc alloc;
+    // a lone game's coded form (launch_quad_code) for its current blocks:
+    // -1 not sought, 0 not used, 1 used
+    int coded = -1;
+    char *code = nullptr;  // codes, values, counts and status, in one allocation
+    size_t code_bytes = 0;
+    size_t o_dict = 0, o_count = 0;
+    uint32_t code_values = 0;  // values of all blocks
 };
 
 // One game held by an engine.
@@ -383,6 +390,8 @@ struct Engine {
     // games of `set` (waits for their admission copies and for the stream).
     int ensure_quads(const std::vector<int> &set);
     void drop_quads(Slot &s, int which);
+    // A lone game's quads in coded form, where its values allow it.
+    int ensure_codes();
     int grow_quads(int which, int64_t need);
     // Allocates both products' quad stores with room for n quads each (and
     // their row pointers); growth then starts from there.

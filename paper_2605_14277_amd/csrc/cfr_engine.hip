@@ -1050,6 +1050,7 @@ void Engine::release()
         if (Q.ptr) (void)hipFree(Q.ptr);
         if (Q.idx) (void)hipFree(Q.idx);
         if (Q.val) (void)hipFree(Q.val);
+        if (Q.code) (void)hipFree(Q.code);
         Q = QuadStore();
     }
 }
@@ -1079,6 +1080,7 @@ void Engine::partition(Slot &s, int which)
 {
     const int k = (int)(&s - slots.data());
     s.blocks[which].clear();
+    quad[which].coded = -1;  // codes belong to blocks
     const bool quads = vec[which] == 3;
     // stream form 3 partitions the game's quads, once they are built
     if (quads && s.qb[which] < 0) return;
@@ -1254,6 +1256,67 @@ int Engine::ensure_quads(const std::vector<int> &set)
             partition(s, w);
         }
         drop_graph();
+    }
+    return CFR_OK;
+}
+
+int Engine::ensure_codes()
+{
+    for (int w = 0; w < 2; ++w) {
+        QuadStore &Q = quad[w];
+        if (!lone || no_alloc || vec[w] != 3 || Q.coded >= 0) continue;
+        Q.coded = 0;
+        const Slot &s = slots[0];
+        const size_t blocks = s.blocks[w].size(), V = value_bytes(prec);
+        if (s.nq[w] < kCodeMinQuads || blocks == 0) continue;
+        size_t at = 8 * (size_t)(s.qb[w] + s.nq[w]);
+        auto take = [&at](size_t bytes) {
+            at = (at + 255) & ~(size_t)255;
+            const size_t a = at;
+            at += bytes;
+            return a;
+        };
+        const size_t o_dict = take(blocks * kCodes * V), o_count = take(4 * blocks),
+                     o_status = take(8);
+        if (at > Q.code_bytes) {
+            if (Q.code) (void)hipFree(Q.code);
+            Q.code = nullptr;
+            Q.code_bytes = 0;
+            void *p = nullptr;
+            if (hipMalloc(&p, at) != hipSuccess) {
+                (void)hipGetLastError();
+                continue;  // the quads as they are
+            }
+            Q.code = (char *)p;
+            Q.code_bytes = at;
+        }
+        uint32_t status[2] = {0, 0};
+        hipError_t e = hipMemsetAsync(Q.code + o_status, 0, 8, st);
+        if (e == hipSuccess)
+            e = launch_quad_code(prec, w == 0 ? it.csr : it.csc, w == 0 ? it.n_csr : it.n_csc, Q.idx,
+                                 Q.val, Q.code, Q.code + o_dict, (int32_t *)(Q.code + o_count),
+                                 (uint32_t *)(Q.code + o_status), st);
+        if (e == hipSuccess)
+            e = hipMemcpyAsync(status, Q.code + o_status, 8, hipMemcpyDeviceToHost, st);
+        if (e == hipSuccess) e = hipStreamSynchronize(st);
+        if (e != hipSuccess) return device_error("quad codes", e);
+        if (status[0]) {
+            (void)hipFree(Q.code);
+            Q.code = nullptr;
+            Q.code_bytes = 0;
+            continue;
+        }
+        Q.o_dict = o_dict;
+        Q.o_count = o_count;
+        Q.code_values = status[1];
+        Q.coded = 1;
+    }
+    // what the products then read of the stream
+    for (int w = 0; w < 2; ++w) {
+        if (!lone || vec[w] != 3 || quad[w].coded != 1) continue;
+        const double V = (double)value_bytes(prec);
+        it.bytes[w] += 8.0 * (double)slots[0].nq[w] - (4.0 + 4.0 * V) * (double)slots[0].nq[w] +
+                       4.0 * (double)slots[0].blocks[w].size() + V * quad[w].code_values;
     }
     return CFR_OK;
 }
@@ -1818,6 +1881,11 @@ int Engine::rebuild()
         it.valid = false;
         return rc;
     }
+    rc = ensure_codes();
+    if (rc) {
+        it.valid = false;
+        return rc;
+    }
     // a batch whose only iterating game can use that game's own structures
     if (!lone) {
         e = single_plans(act.size() == 1 ? act[0] : -1, st);
@@ -1897,17 +1965,30 @@ hipError_t Engine::spmv(const Tables &T, int which, const void *xin, void *yout,
     const int32_t *rp = quads ? quad[which].ptr : ptr[which];
     const int32_t *ix = quads ? (const int32_t *)quad[which].idx : idx[which];
     const void *vl = quads ? quad[which].val : val[which];
+    // (codes belong to the iteration's blocks; a lone game is evaluated over
+    // the same ones)
+    const bool coded = quads && quad[which].coded == 1 && &T == &it;
+    const QuadStore &Q = quad[which];
     if (timed) {
         hipEvent_t a, b;
         hipError_t e = hipEventCreate(&a);
         if (e == hipSuccess) e = hipEventCreate(&b);
         if (e != hipSuccess) return e;
-        e = launch_spmv(prec, items[which], vec[which], tab, n, rp, ix, vl, xin, yout, remap,
-                        sequential(), begin ? 1 : 0, sc, s, a, b);
+        if (coded)
+            e = launch_spmv_coded(prec, items[which], tab, n, rp, Q.code, Q.code + Q.o_dict,
+                                  (const int32_t *)(Q.code + Q.o_count), xin, yout, remap,
+                                  sequential(), begin ? 1 : 0, sc, s, a, b);
+        else
+            e = launch_spmv(prec, items[which], vec[which], tab, n, rp, ix, vl, xin, yout, remap,
+                            sequential(), begin ? 1 : 0, sc, s, a, b);
         events[which].emplace_back(a, b);
         launches[which]++;
         return e;
     }
+    if (coded)
+        return launch_spmv_coded(prec, items[which], tab, n, rp, Q.code, Q.code + Q.o_dict,
+                                 (const int32_t *)(Q.code + Q.o_count), xin, yout, remap,
+                                 sequential(), begin ? 1 : 0, sc, s);
     return launch_spmv(prec, items[which], vec[which], tab, n, rp, ix, vl, xin, yout, remap,
                        sequential(), begin ? 1 : 0, sc, s);
 }

@@ -254,6 +254,27 @@ hipError_t launch_quad_fill(int prec, const int32_t *ptr, const int32_t *idx, co
                             int64_t nb, int32_t row0, int32_t nr, const int32_t *qptr, int64_t qb,
                             uint32_t *qidx, void *qval, hipStream_t st);
 
+// Coded form of one product's quads (blocks of `tab`; one pass over the quads):
+// code: two 32-bit words a quad (aligned group; four codes), dict: kCodes
+// values a block, n_dict: how many of them.  status (two words, zeroed by the
+// caller): [0] some block has too many distinct values, the rest is then
+// unusable; [1] values of all blocks.
+constexpr int kCodes = 255;
+// Smallest product (quads) whose coded form is sought.  Below it a product is
+// bound by its launch and its load chain (150000 quads: 4.9 us plain, 5.0
+// coded); 490000 take 8.4 us plain and 8.1 coded in FP32_ACC64, 11.0 and 9.1
+// in FP64; 2.0 million 10.5 and 9.2, 18.3 and 13.8.
+constexpr int64_t kCodeMinQuads = 1 << 18;
+hipError_t launch_quad_code(int prec, const SpmvBlock *tab, int32_t n_tab, const uint32_t *qidx,
+                            const void *qval, void *code, void *dict, int32_t *n_dict,
+                            uint32_t *status, hipStream_t st);
+// launch_spmv over the coded form (same blocks, 8 or 16 nonzeros a thread).
+hipError_t launch_spmv_coded(int prec, int items, const SpmvBlock *tab, int32_t n_tab,
+                             const int32_t *ptr, const void *code, const void *dict,
+                             const int32_t *n_dict, const void *xin, void *yout, int xcd_remap,
+                             int sequential, int begin, Scalars *sc, hipStream_t st,
+                             hipEvent_t start = nullptr, hipEvent_t stop = nullptr);
+
 size_t value_bytes(int prec);
 size_t accum_bytes(int prec);
 size_t compute_bytes(int prec);

@@ -185,6 +185,50 @@ __device__ __noinline__ void begin_iteration_in(Scalars *sc)
 // Payoff product y = M x over a row-sorted matrix
 // ---------------------------------------------------------------------------
 
+// The rows of one block from their staged products (row r's are
+// prod[s_ptr[r] .. s_ptr[r + 1])).  n, per: stream elements of the block and
+// staging slots each.
+template <int P, bool SEQ, typename L>
+__device__ __forceinline__ void spmv_row_sums(const L *prod, const int32_t *s_ptr, int32_t rb,
+                                              int32_t nr, int32_t n, int32_t per,
+                                              typename Types<P>::V *__restrict__ yout)
+{
+    using V = typename Types<P>::V;
+    using C = typename Types<P>::C;
+    const int tid = threadIdx.x;
+    if (SEQ) {
+        if (tid < nr) {
+            int32_t i = s_ptr[tid];
+            const int32_t z = s_ptr[tid + 1];
+            C acc = 0;
+            for (; i + 4 <= z; i += 4) {
+                C q0 = prod[i], q1 = prod[i + 1], q2 = prod[i + 2], q3 = prod[i + 3];
+                acc = acc + q0;
+                acc = acc + q1;
+                acc = acc + q2;
+                acc = acc + q3;
+            }
+            for (; i < z; ++i) acc = acc + (C)prod[i];
+            yout[rb + tid] = (V)acc;
+        }
+        return;
+    }
+    // lanes per row: the largest power of two (<= 64) that still gives every
+    // row of the block its own group, and not far above the mean row length
+    int Lr = 64;
+    while (Lr > 1 && Lr * nr > kSpmvThreads) Lr >>= 1;
+    while (Lr > 1 && Lr > 2 * (per * n / nr + 1)) Lr >>= 1;
+    const int lane = tid & (Lr - 1);
+    const int groups = kSpmvThreads / Lr;
+    for (int32_t r = tid / Lr; r < nr; r += groups) {
+        const int32_t a = s_ptr[r], z = s_ptr[r + 1];
+        C acc = 0;
+        for (int32_t i = a + lane; i < z; i += Lr) acc = acc + (C)prod[i];
+        for (int off = Lr >> 1; off > 0; off >>= 1) acc = acc + __shfl_xor(acc, off, Lr);
+        if (lane == 0) yout[rb + r] = (V)acc;
+    }
+}
+
 // SEQ: every row is summed strictly left to right (the order of a plain
 // sequential loop), which the FP64 path needs to reproduce a sequential
 // evaluation bit for bit; otherwise a power-of-two group of lanes shares
@@ -465,37 +509,7 @@ __device__ __forceinline__ void spmv_blocks(
     if (tid < nr) s_ptr[tid] = per * (pr - p0) + sh;
     if (tid == 0) s_ptr[nr] = per * n + sh;
     __syncthreads();
-    if (SEQ) {
-        if (tid < nr) {
-            int32_t i = s_ptr[tid];
-            const int32_t z = s_ptr[tid + 1];
-            C acc = 0;
-            for (; i + 4 <= z; i += 4) {
-                C q0 = prod[i], q1 = prod[i + 1], q2 = prod[i + 2], q3 = prod[i + 3];
-                acc = acc + q0;
-                acc = acc + q1;
-                acc = acc + q2;
-                acc = acc + q3;
-            }
-            for (; i < z; ++i) acc = acc + (C)prod[i];
-            yout[rb + tid] = (V)acc;
-        }
-        return;
-    }
-    // lanes per row: the largest power of two (<= 64) that still gives every
-    // row of the block its own group, and not far above the mean row length
-    int Lr = 64;
-    while (Lr > 1 && Lr * nr > kSpmvThreads) Lr >>= 1;
-    while (Lr > 1 && Lr > 2 * (per * n / nr + 1)) Lr >>= 1;
-    const int lane = tid & (Lr - 1);
-    const int groups = kSpmvThreads / Lr;
-    for (int32_t r = tid / Lr; r < nr; r += groups) {
-        const int32_t a = s_ptr[r], z = s_ptr[r + 1];
-        C acc = 0;
-        for (int32_t i = a + lane; i < z; i += Lr) acc = acc + (C)prod[i];
-        for (int off = Lr >> 1; off > 0; off >>= 1) acc = acc + __shfl_xor(acc, off, Lr);
-        if (lane == 0) yout[rb + r] = (V)acc;
-    }
+    spmv_row_sums<P, SEQ>(prod, s_ptr, rb, nr, n, per, yout);
 }
 
 #define CFR_SPMV_PARAMS(P)                                                                    \
@@ -521,6 +535,128 @@ __global__ __launch_bounds__(kSpmvThreads, 8) void k_spmv_quads(CFR_SPMV_PARAMS(
     spmv_blocks<P, false, ITEMS, 3>(n_blk, tab, ptr, idx, val, xin, yout, xcd_remap, begin, sc);
 }
 #undef CFR_SPMV_PARAMS
+
+// Stream form 3 with coded values.  Payoffs of a game usually take few
+// distinct values near each other (a terminal's payoff recurs for many pairs
+// of signals): where no block holds more than kCodes of them, a quad is its
+// aligned group and four 8-bit codes, eight bytes instead of 20 (FP32) or 36,
+// and the block's values come with it once.  Code 0 stands for an absent
+// position: it multiplies -0.0 by +0, which leaves every sum unchanged.  The
+// products, their rounding and the order of the sums are those of the quads
+// they stand for (a float product is exact in double, so the fused
+// multiply-add of the ACC64 mode rounds as the addition alone does), so the
+// results are the same bit for bit.
+// What bounds it: the large showdown game's streams (9.3e7 nonzeros,
+// FP32_ACC64) shrink from 564 and 616 MB to 216 and 233 MB and its products
+// from 93 and 103 us to 63 and 73; the loads' latency (65 % of the wave
+// cycles wait) and 190 vector instructions a wave now weigh more than the
+// stream.  2.3e7 nonzeros in FP64: 51 and 62 us before, 34 and 33 now.
+template <int P, bool SEQ, int NQ>
+__global__ __launch_bounds__(kSpmvThreads, P == CFR_FP64 ? 4 : 8) void k_spmv_coded(
+    int32_t n_blk, const SpmvBlock *__restrict__ tab, const int32_t *__restrict__ ptr,
+    const uint2 *__restrict__ code, const typename Types<P>::V *__restrict__ dict,
+    const int32_t *__restrict__ n_dict, const typename Types<P>::V *__restrict__ xin,
+    typename Types<P>::V *__restrict__ yout, int xcd_remap, int begin, Scalars *sc)
+{
+    using V = typename Types<P>::V;
+    using C = typename Types<P>::C;
+    using L = typename std::conditional<(CFR_SPMV_LDS_VALUE != 0) && P != CFR_FP64, V, C>::type;
+    typedef uint32_t v2u __attribute__((ext_vector_type(2)));
+    constexpr int kCap = kSpmvThreads * NQ;  // quads
+    __shared__ L prod[SEQ ? 4 * kCap : kCap];
+    __shared__ int32_t s_ptr[kSpmvRowCap + 1];
+    __shared__ C values[kCodes + 1];
+    __shared__ C red[kSpmvThreads];
+
+    int32_t bid = (int32_t)blockIdx.x;
+    if (xcd_remap) {
+        const int32_t per = (n_blk + 7) / 8;
+        bid = (int32_t)(blockIdx.x % 8) * per + (int32_t)(blockIdx.x / 8);
+    }
+    if (bid >= n_blk) return;
+    const int tid = threadIdx.x;
+    const SpmvBlock bk = tab[bid];
+    const int32_t nd = n_dict[bid];
+    if (begin && bk.begin && tid == 0) begin_iteration_in<true>(sc + bk.slot);
+    const int32_t rb = bk.row0, nr = bk.nr, n = bk.n, p0 = bk.p0;
+    const v2u *const qp = (const v2u *)code + bk.e0;
+    const V *const dv = dict + (int64_t)bid * kCodes;
+    if (tid < nd) values[1 + tid] = (C)dv[tid];
+    if (tid == 0) values[0] = (C)(-0.0);
+
+    // a quad's present positions, in order
+    auto position = [&](uint32_t c, V x, int k, C &v, C &xv) __attribute__((always_inline)) {
+        const uint32_t e = (c >> (8 * k)) & 255u;
+        v = values[e];
+        xv = (C)(e ? x : (V)0);
+    };
+    if (n > kCap) {
+        // a single long row, as spmv_blocks sums it
+        __syncthreads();
+        C acc = 0;
+        for (int32_t i = tid; i < n; i += kSpmvThreads) {
+            const v2u q = qp[i];
+            const int64_t c0 = 4 * (int64_t)(q.x & kQuadIndexMask);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                C v, xv;
+                position(q.y, xin[c0 + k], k, v, xv);
+                acc = acc + v * xv;
+            }
+        }
+        red[tid] = acc;
+        __syncthreads();
+        for (int w = kSpmvThreads / 2; w > 0; w >>= 1) {
+            if (tid < w) red[tid] = red[tid] + red[tid + w];
+            __syncthreads();
+        }
+        if (tid == 0) yout[rb] = (V)red[0];
+        return;
+    }
+    const int32_t pr = ptr[rb + (tid < nr ? tid : 0)];
+    if (n > 0) {
+        v2u qd[NQ];
+        V gx[NQ][4];
+#pragma unroll
+        for (int j = 0; j < NQ; ++j) {
+            const int32_t qi = j * kSpmvThreads + tid;
+            qd[j] = __builtin_nontemporal_load(qp + (qi < n ? qi : 0));
+        }
+#pragma unroll
+        for (int j = 0; j < NQ; ++j)
+            load4_cached(xin + 4 * (int64_t)(qd[j].x & kQuadIndexMask), gx[j]);
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < NQ; ++j) {
+            const int32_t qi = j * kSpmvThreads + tid;
+            if (SEQ) {
+                L o[4];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    C v, xv;
+                    position(qd[j].y, gx[j][k], k, v, xv);
+                    o[k] = (L)(v * xv);
+                }
+                store4(&prod[4 * qi], o);  // slots past the block are no row's
+            } else {
+                C qs = (C)(-0.0);
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    C v, xv;
+                    position(qd[j].y, gx[j][k], k, v, xv);
+                    if constexpr (P == CFR_FP32_ACC64) qs = __builtin_fma(v, xv, qs);
+                    else qs = qs + v * xv;
+                }
+                prod[qi] = (L)qs;
+            }
+        }
+    }
+    constexpr int32_t per = SEQ ? 4 : 1;
+    if (tid < nr) s_ptr[tid] = per * (pr - p0);
+    if (tid == 0) s_ptr[nr] = per * n;
+    __syncthreads();
+    spmv_row_sums<P, SEQ>(prod, s_ptr, rb, nr, n, per, yout);
+}
 
 // ---------------------------------------------------------------------------
 // ObserveUtility for one level, fused with the variant and regret matching
@@ -1691,6 +1827,98 @@ __global__ __launch_bounds__(kThreads) void k_quad_fill(
     }
 }
 
+// Codes of one product's quads, a workgroup per product block: the block's
+// distinct values are collected in a hash table in LDS, numbered, and every
+// position is looked up.  status[0] is set when some block has more than
+// kCodes of them (its codes are then not written), status[1] counts the
+// values of all blocks.  A value's bits are its key; the empty key is a NaN's,
+// which no payoff has.
+constexpr int kCodeSlots = 1024;
+template <int P>
+__global__ __launch_bounds__(kThreads) void k_quad_code(const SpmvBlock *__restrict__ tab,
+                                                        const uint32_t *__restrict__ qidx,
+                                                        const typename Types<P>::V *__restrict__ qval,
+                                                        uint2 *__restrict__ code,
+                                                        typename Types<P>::V *__restrict__ dict,
+                                                        int32_t *__restrict__ n_dict,
+                                                        uint32_t *__restrict__ status)
+{
+    using V = typename Types<P>::V;
+    using K = typename std::conditional<sizeof(V) == 8, unsigned long long, unsigned int>::type;
+    constexpr K kEmpty = ~(K)0;
+    __shared__ K key[kCodeSlots];
+    __shared__ uint32_t num[kCodeSlots];
+    __shared__ uint32_t count, distinct, over;
+    const int tid = threadIdx.x;
+    const SpmvBlock bk = tab[blockIdx.x];
+    for (int i = tid; i < kCodeSlots; i += kThreads) key[i] = kEmpty;
+    if (tid == 0) {
+        count = distinct = 0;
+        over = *(volatile uint32_t *)status;  // some block's were too many: nothing to do
+    }
+    __syncthreads();
+    auto bits = [](V v) {
+        K k;
+        __builtin_memcpy(&k, &v, sizeof k);
+        return k;
+    };
+    auto slot = [](K k) {
+        return (uint32_t)(((unsigned long long)k * 0x9E3779B97F4A7C15ull) >> 54) & (kCodeSlots - 1);
+    };
+    for (int32_t i = tid; i < bk.n && !over; i += kThreads) {
+        const int64_t q = bk.e0 + i;
+        const uint32_t mask = qidx[q] >> kQuadMaskShift;
+        for (int k = 0; k < 4; ++k) {
+            if (!((mask >> k) & 1u)) continue;
+            const K v = bits(qval[4 * q + k]);
+            uint32_t h = slot(v);
+            // (at most kCodes + kThreads slots are ever taken, so a free one
+            // is found)
+            while (*(volatile uint32_t *)&distinct <= (uint32_t)kCodes) {
+                const K was = atomicCAS(&key[h], kEmpty, v);
+                if (was == kEmpty) atomicAdd(&distinct, 1u);
+                if (was == kEmpty || was == v) break;
+                h = (h + 1) & (kCodeSlots - 1);
+            }
+        }
+        if (*(volatile uint32_t *)&distinct > (uint32_t)kCodes) break;
+    }
+    __syncthreads();
+    if (over || distinct > (uint32_t)kCodes) {
+        if (tid == 0) {
+            n_dict[blockIdx.x] = 0;
+            atomicOr(&status[0], 1u);
+        }
+        return;
+    }
+    for (int i = tid; i < kCodeSlots; i += kThreads)
+        if (key[i] != kEmpty) {
+            const uint32_t c = atomicAdd(&count, 1u);
+            num[i] = c + 1;
+            V v;
+            __builtin_memcpy(&v, &key[i], sizeof v);
+            dict[(int64_t)blockIdx.x * kCodes + c] = v;
+        }
+    __syncthreads();
+    for (int32_t i = tid; i < bk.n; i += kThreads) {
+        const int64_t q = bk.e0 + i;
+        const uint32_t w = qidx[q], mask = w >> kQuadMaskShift;
+        uint32_t c = 0;
+        for (int k = 0; k < 4; ++k) {
+            if (!((mask >> k) & 1u)) continue;
+            const K v = bits(qval[4 * q + k]);
+            uint32_t h = slot(v);
+            while (key[h] != v) h = (h + 1) & (kCodeSlots - 1);
+            c |= num[h] << (8 * k);
+        }
+        code[q] = make_uint2(w & kQuadIndexMask, c);
+    }
+    if (tid == 0) {
+        n_dict[blockIdx.x] = (int32_t)count;
+        atomicAdd(&status[1], count);
+    }
+}
+
 // ---------------------------------------------------------------------------
 // Launch helpers
 // ---------------------------------------------------------------------------
@@ -2221,6 +2449,72 @@ hipError_t launch_quad_fill(int prec, const int32_t *ptr, const int32_t *idx, co
                             uint32_t *qidx, void *qval, hipStream_t st)
 {
     CFR_DISPATCH(prec, quad_fill_t<P>(ptr, idx, val, nb, row0, nr, qptr, qb, qidx, qval, st));
+}
+
+template <int P>
+hipError_t quad_code_t(const SpmvBlock *tab, int32_t n_tab, const uint32_t *qidx, const void *qval,
+                       void *code, void *dict, int32_t *n_dict, uint32_t *status, hipStream_t st)
+{
+    using V = typename Types<P>::V;
+    if (n_tab <= 0) return hipSuccess;
+    hipLaunchKernelGGL((k_quad_code<P>), dim3((unsigned)n_tab), dim3(kThreads), 0, st, tab, qidx,
+                       (const V *)qval, (uint2 *)code, (V *)dict, n_dict, status);
+    return hipGetLastError();
+}
+
+hipError_t launch_quad_code(int prec, const SpmvBlock *tab, int32_t n_tab, const uint32_t *qidx,
+                            const void *qval, void *code, void *dict, int32_t *n_dict,
+                            uint32_t *status, hipStream_t st)
+{
+    CFR_DISPATCH(prec, quad_code_t<P>(tab, n_tab, qidx, qval, code, dict, n_dict, status, st));
+}
+
+template <int P, bool SEQ, int NQ>
+hipError_t spmv_coded_launch(const SpmvBlock *tab, int32_t n_tab, const int32_t *ptr,
+                             const void *code, const void *dict, const int32_t *n_dict,
+                             const void *xin, void *yout, int xcd_remap, int begin, Scalars *sc,
+                             hipStream_t st, hipEvent_t ev0, hipEvent_t ev1)
+{
+    using V = typename Types<P>::V;
+    const unsigned grid = xcd_remap ? (unsigned)(((n_tab + 7) / 8) * 8) : (unsigned)n_tab;
+    if (ev0)
+        hipExtLaunchKernelGGL((k_spmv_coded<P, SEQ, NQ>), dim3(grid), dim3(kSpmvThreads), 0, st, ev0,
+                              ev1, 0u, n_tab, tab, ptr, (const uint2 *)code, (const V *)dict, n_dict,
+                              (const V *)xin, (V *)yout, xcd_remap, begin, sc);
+    else
+        hipLaunchKernelGGL((k_spmv_coded<P, SEQ, NQ>), dim3(grid), dim3(kSpmvThreads), 0, st, n_tab,
+                           tab, ptr, (const uint2 *)code, (const V *)dict, n_dict, (const V *)xin,
+                           (V *)yout, xcd_remap, begin, sc);
+    return hipGetLastError();
+}
+
+template <int P>
+hipError_t spmv_coded_t(int items, const SpmvBlock *tab, int32_t n_tab, const int32_t *ptr,
+                        const void *code, const void *dict, const int32_t *n_dict, const void *xin,
+                        void *yout, int xcd_remap, int sequential, int begin, Scalars *sc,
+                        hipStream_t st, hipEvent_t ev0, hipEvent_t ev1)
+{
+#define CFR_CODED(SQ, NQ)                                                                     \
+    return spmv_coded_launch<P, SQ, NQ>(tab, n_tab, ptr, code, dict, n_dict, xin, yout,       \
+                                        xcd_remap, begin, sc, st, ev0, ev1)
+    if (n_tab <= 0 || (items != 8 && items != 16)) return hipErrorInvalidValue;
+    if (items == 8) {
+        if (sequential) CFR_CODED(true, 2);
+        CFR_CODED(false, 2);
+    }
+    if (sequential) CFR_CODED(true, 4);
+    CFR_CODED(false, 4);
+#undef CFR_CODED
+}
+
+hipError_t launch_spmv_coded(int prec, int items, const SpmvBlock *tab, int32_t n_tab,
+                             const int32_t *ptr, const void *code, const void *dict,
+                             const int32_t *n_dict, const void *xin, void *yout, int xcd_remap,
+                             int sequential, int begin, Scalars *sc, hipStream_t st,
+                             hipEvent_t start, hipEvent_t stop)
+{
+    CFR_DISPATCH(prec, spmv_coded_t<P>(items, tab, n_tab, ptr, code, dict, n_dict, xin, yout,
+                                       xcd_remap, sequential, begin, sc, st, start, stop));
 }
 
 hipError_t launch_remap(int32_t *a, int64_t n, const int32_t *map, hipStream_t st)
