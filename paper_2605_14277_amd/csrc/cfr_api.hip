@@ -618,11 +618,7 @@ int cfr_strategy(cfr_solver *s, int player, int kind, double *out, int64_t len)
     if (len != s->eng.slots[0].n_seq[player]) return fail(CFR_EINVAL, "output length must equal n_seq");
     try {
         DeviceGuard guard(s->eng.device);
-        std::vector<double> v;
-        int rc = s->eng.fetch_vector(0, player, kind == CFR_AVERAGE ? 1 : 0, v);
-        if (rc) return rc;
-        std::memcpy(out, v.data(), sizeof(double) * v.size());
-        return CFR_OK;
+        return s->eng.fetch_vector(0, player, kind == CFR_AVERAGE ? 1 : 0, out);
     } catch (const std::exception &ex) {
         return fail(CFR_ENOMEM, std::string("host allocation failed: ") + ex.what());
     }
@@ -636,11 +632,7 @@ int cfr_regrets(cfr_solver *s, int player, double *out, int64_t len)
     if (len != s->eng.slots[0].n_seq[player]) return fail(CFR_EINVAL, "output length must equal n_seq");
     try {
         DeviceGuard guard(s->eng.device);
-        std::vector<double> v;
-        int rc = s->eng.fetch_vector(0, player, 2, v);
-        if (rc) return rc;
-        std::memcpy(out, v.data(), sizeof(double) * v.size());
-        return CFR_OK;
+        return s->eng.fetch_vector(0, player, 2, out);
     } catch (const std::exception &ex) {
         return fail(CFR_ENOMEM, std::string("host allocation failed: ") + ex.what());
     }
@@ -1238,11 +1230,7 @@ int cfr_batch_strategy(cfr_batch *b, int64_t id, int player, int kind, double *o
         return fail(CFR_EINVAL, "output length must equal n_seq");
     try {
         DeviceGuard guard(b->eng.device);
-        std::vector<double> v;
-        int rc = b->eng.fetch_vector(k, player, kind == CFR_AVERAGE ? 1 : 0, v);
-        if (rc) return rc;
-        std::memcpy(out, v.data(), sizeof(double) * v.size());
-        return CFR_OK;
+        return b->eng.fetch_vector(k, player, kind == CFR_AVERAGE ? 1 : 0, out);
     } catch (const std::exception &ex) {
         return fail(CFR_ENOMEM, std::string("host allocation failed: ") + ex.what());
     }

@@ -168,6 +168,12 @@ struct RangeAlloc {
     int64_t largest() const;
 };
 
+// Staging of fetch_vector: room for the scalars, and the longest part (512
+// KiB of doubles stay in the host's caches while the next part arrives).
+constexpr size_t kExportHead = 256;
+constexpr int32_t kExportPart = 1 << 16;
+static_assert(sizeof(Scalars) <= kExportHead && sizeof(Scalars) % 8 == 0, "export head");
+
 // Stream form 3 of one product: a derived copy of every game's matrix in
 // quads, in memory the engine allocates itself on first use and grows when
 // needed.  Each game owns a range of quads, built on the device from its
@@ -213,6 +219,7 @@ struct Slot {
     int64_t nq[2] = {0, 0};              // quads in it
     std::vector<int32_t> qptr[2];        // its local quad row pointers
     std::vector<int32_t> old_of_new[2];  // internal -> caller numbering
+    bool same_order[2] = {false, false};  // the two are alike
     std::vector<SpmvBlock> blocks[2];    // product blocks (global fields)
     // the resident loop: the treeplexes it is planned from (null when the
     // game has too many sequences for it), and the plan for the current
@@ -323,6 +330,11 @@ struct Engine {
     bool pending = false;
     std::vector<int> pending_set;
     Scalars *eval_stage = nullptr;
+    // Page-locked staging of fetch_vector, made by the first one: a game's
+    // scalars, then two parts of exp_part sequences each.
+    char *exp_stage = nullptr;
+    int32_t exp_part = 0;
+    hipEvent_t exp_ev[2] = {nullptr, nullptr};
     hipEvent_t eval_ev = nullptr;
 
     // host-side time and calls per activity (kHost* below), for reports
@@ -451,7 +463,8 @@ struct Engine {
     // Times `reps` launches of one product with the current tiling (ms each).
     int time_spmv(int which, int reps, double *ms);
 
-    int fetch_vector(int slot, int player, int what, std::vector<double> &out);
+    int fetch_vector(int slot, int player, int what, double *out);
+    bool export_ready(int32_t n);
 };
 
 }  // namespace cfr

@@ -224,6 +224,10 @@ hipError_t launch_shallow(int prec, int variant, const DevPlayer &p, double usig
 hipError_t launch_normalize(int prec, const RangeBlock *tab, int32_t n_tab, const DevPlayer &p,
                             const Scalars *sc, hipStream_t st);
 // One level of the best-response max-sweep (values in vinf).
+// Sequences [lo, hi) of one game's vector (x and acc start at the game) as
+// doubles into page-locked memory, and with lo 0 its scalars into head.
+hipError_t launch_export(int prec, const void *x, const void *acc, const Scalars *sc, int what,
+                         int32_t lo, int32_t hi, double *out, Scalars *head, hipStream_t st);
 hipError_t launch_br(int prec, const RangeBlock *tab, int32_t n_tab, const DevPlayer &p,
                      double usign, hipStream_t st);
 // Per game: usign*g[root] + sum of vinf over the root decision points,

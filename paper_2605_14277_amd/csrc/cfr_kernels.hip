@@ -1629,6 +1629,32 @@ __global__ __launch_bounds__(kThreads) void k_normalize(const RangeBlock *__rest
     xbar[i] = i == rb.aux ? (V)1 : W > 0 ? (V)((double)s[i] / W) : x[i];
 }
 
+// A vector of one game as the caller sees it, sequences [lo, hi) of it, into
+// page-locked host memory: what 0 the current strategy, 1 the average (the
+// current one before the first iteration), 2 the regrets.  The first part
+// brings the game's scalars along.
+template <int P>
+__global__ __launch_bounds__(kThreads) void k_export(const typename Types<P>::V *__restrict__ x,
+                                                     const typename Types<P>::R *__restrict__ acc,
+                                                     const Scalars *__restrict__ sc, int what,
+                                                     int32_t lo, int32_t hi,
+                                                     double *__restrict__ out,
+                                                     Scalars *__restrict__ head)
+{
+    const int32_t i = lo + (int32_t)(blockIdx.x * kThreads + threadIdx.x);
+    constexpr int kWords = (int)(sizeof(Scalars) / 8);
+    if (lo == 0 && i < kWords) ((double *)head)[i] = ((const double *)sc)[i];
+    if (i >= hi) return;
+    double v;
+    if (what == 0 || (what == 1 && sc->W <= 0))
+        v = (double)x[i];
+    else if (i == 0)
+        v = what == 1 ? 1.0 : 0.0;
+    else
+        v = what == 1 ? (double)acc[i] / sc->W : (double)acc[i];
+    out[i - lo] = v;
+}
+
 template <int P>
 __global__ __launch_bounds__(kThreads) void k_br(const RangeBlock *__restrict__ tab,
                                                  const int32_t *__restrict__ inf_first,
@@ -2274,6 +2300,18 @@ hipError_t normalize_t(const RangeBlock *tab, int32_t n_tab, const DevPlayer &p,
 }
 
 template <int P>
+hipError_t export_t(const void *x, const void *acc, const Scalars *sc, int what, int32_t lo,
+                    int32_t hi, double *out, Scalars *head, hipStream_t st)
+{
+    using T = Types<P>;
+    if (hi <= lo) return hipSuccess;
+    const unsigned grid = (unsigned)((hi - lo + kThreads - 1) / kThreads);
+    hipLaunchKernelGGL((k_export<P>), dim3(grid), dim3(kThreads), 0, st, (const typename T::V *)x,
+                       (const typename T::R *)acc, sc, what, lo, hi, out, head);
+    return hipGetLastError();
+}
+
+template <int P>
 hipError_t br_t(const RangeBlock *tab, int32_t n_tab, const DevPlayer &p, double usign,
                 hipStream_t st)
 {
@@ -2382,6 +2420,12 @@ hipError_t launch_normalize(int prec, const RangeBlock *tab, int32_t n_tab, cons
                             const Scalars *sc, hipStream_t st)
 {
     CFR_DISPATCH(prec, normalize_t<P>(tab, n_tab, p, sc, st));
+}
+
+hipError_t launch_export(int prec, const void *x, const void *acc, const Scalars *sc, int what,
+                         int32_t lo, int32_t hi, double *out, Scalars *head, hipStream_t st)
+{
+    CFR_DISPATCH(prec, export_t<P>(x, acc, sc, what, lo, hi, out, head, st));
 }
 
 hipError_t launch_br(int prec, const RangeBlock *tab, int32_t n_tab, const DevPlayer &p,
