@@ -145,6 +145,21 @@ __device__ __forceinline__ void store4(double *p, const double (&o)[4])
     *(v2d *)p = v2d{o[0], o[1]};
     *((v2d *)p + 1) = v2d{o[2], o[3]};
 }
+// Four aligned values staged in LDS.
+__device__ __forceinline__ void load4_lds(const float *p, float (&o)[4])
+{
+    const v4f a = *(const v4f *)p;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) o[k] = a[k];
+}
+__device__ __forceinline__ void load4_lds(const double *p, double (&o)[4])
+{
+    const v2d a = *(const v2d *)p, b = *((const v2d *)p + 1);
+    o[0] = a[0];
+    o[1] = a[1];
+    o[2] = b[0];
+    o[3] = b[1];
+}
 
 // ---------------------------------------------------------------------------
 // Per-iteration scalars
@@ -215,9 +230,10 @@ __device__ __forceinline__ void spmv_row_sums(const L *prod, const int32_t *s_pt
     }
     // lanes per row: the largest power of two (<= 64) that still gives every
     // row of the block its own group, and not far above the mean row length
+    // (Lr <= 2 * (per * n / nr + 1), written without the division)
     int Lr = 64;
     while (Lr > 1 && Lr * nr > kSpmvThreads) Lr >>= 1;
-    while (Lr > 1 && Lr > 2 * (per * n / nr + 1)) Lr >>= 1;
+    while (Lr > 1 && per * n < (Lr / 2 - 1) * nr) Lr >>= 1;
     const int lane = tid & (Lr - 1);
     const int groups = kSpmvThreads / Lr;
     for (int32_t r = tid / Lr; r < nr; r += groups) {
@@ -536,6 +552,13 @@ __global__ __launch_bounds__(kSpmvThreads, 8) void k_spmv_quads(CFR_SPMV_PARAMS(
 }
 #undef CFR_SPMV_PARAMS
 
+// Workgroups of k_spmv_coded a compute unit holds: staging every position
+// takes 38 KB of LDS, FP64 without it 78 registers.
+constexpr int coded_blocks_per_cu(int prec, bool seq)
+{
+    return seq ? 4 : prec == CFR_FP64 ? 6 : 8;
+}
+
 // Stream form 3 with coded values.  Payoffs of a game usually take few
 // distinct values near each other (a terminal's payoff recurs for many pairs
 // of signals): where no block holds more than kCodes of them, a quad is its
@@ -548,11 +571,15 @@ __global__ __launch_bounds__(kSpmvThreads, 8) void k_spmv_quads(CFR_SPMV_PARAMS(
 // results are the same bit for bit.
 // What bounds it: the large showdown game's streams (9.3e7 nonzeros,
 // FP32_ACC64) shrink from 564 and 616 MB to 216 and 233 MB and its products
-// from 93 and 103 us to 63 and 73; the loads' latency (65 % of the wave
-// cycles wait) and 190 vector instructions a wave now weigh more than the
-// stream.  2.3e7 nonzeros in FP64: 51 and 62 us before, 34 and 33 now.
+// from 93 and 103 us to 63 and 66; 2.3e7 nonzeros in FP64: 51 and 62 us to
+// 30 and 28.  The stream alone takes 42 to 46; the rest is instruction issue
+// (190 vector and 150 scalar ones a wave), not latency.
+// Workgroups stay and take block after block, the next block's codes, row
+// pointers and values under way while one is summed: 73 and 63 us with a
+// workgroup for each block, 34 and 33 in FP64, whose staging leaves four
+// workgroups a compute unit to hide the loads behind.
 template <int P, bool SEQ, int NQ>
-__global__ __launch_bounds__(kSpmvThreads, P == CFR_FP64 ? 4 : 8) void k_spmv_coded(
+__global__ __launch_bounds__(kSpmvThreads, coded_blocks_per_cu(P, SEQ)) void k_spmv_coded(
     int32_t n_blk, const SpmvBlock *__restrict__ tab, const int32_t *__restrict__ ptr,
     const uint2 *__restrict__ code, const typename Types<P>::V *__restrict__ dict,
     const int32_t *__restrict__ n_dict, const typename Types<P>::V *__restrict__ xin,
@@ -563,99 +590,158 @@ __global__ __launch_bounds__(kSpmvThreads, P == CFR_FP64 ? 4 : 8) void k_spmv_co
     using L = typename std::conditional<(CFR_SPMV_LDS_VALUE != 0) && P != CFR_FP64, V, C>::type;
     typedef uint32_t v2u __attribute__((ext_vector_type(2)));
     constexpr int kCap = kSpmvThreads * NQ;  // quads
-    __shared__ L prod[SEQ ? 4 * kCap : kCap];
+    constexpr int32_t per = SEQ ? 4 : 1;     // staging slots a quad
+    __shared__ __attribute__((aligned(16))) L prod[per * kCap];
     __shared__ int32_t s_ptr[kSpmvRowCap + 1];
     __shared__ C values[kCodes + 1];
     __shared__ C red[kSpmvThreads];
 
-    int32_t bid = (int32_t)blockIdx.x;
+    // this workgroup's blocks: first, first + step, ... below last
+    int32_t bid = (int32_t)blockIdx.x, last = n_blk, step = (int32_t)gridDim.x;
     if (xcd_remap) {
-        const int32_t per = (n_blk + 7) / 8;
-        bid = (int32_t)(blockIdx.x % 8) * per + (int32_t)(blockIdx.x / 8);
+        const int32_t each = (n_blk + 7) / 8, xcd = bid % 8;
+        bid = xcd * each + bid / 8;
+        last = xcd * each + each < n_blk ? xcd * each + each : n_blk;
+        step /= 8;
     }
-    if (bid >= n_blk) return;
+    if (bid >= last) return;
     const int tid = threadIdx.x;
-    const SpmvBlock bk = tab[bid];
-    const int32_t nd = n_dict[bid];
-    if (begin && bk.begin && tid == 0) begin_iteration_in<true>(sc + bk.slot);
-    const int32_t rb = bk.row0, nr = bk.nr, n = bk.n, p0 = bk.p0;
-    const v2u *const qp = (const v2u *)code + bk.e0;
-    const V *const dv = dict + (int64_t)bid * kCodes;
-    if (tid < nd) values[1 + tid] = (C)dv[tid];
-    if (tid == 0) values[0] = (C)(-0.0);
+    const v2u *const cp = (const v2u *)code;
 
-    // a quad's present positions, in order
+    // a quad's positions, in order
     auto position = [&](uint32_t c, V x, int k, C &v, C &xv) __attribute__((always_inline)) {
         const uint32_t e = (c >> (8 * k)) & 255u;
         v = values[e];
         xv = (C)(e ? x : (V)0);
     };
-    if (n > kCap) {
-        // a single long row, as spmv_blocks sums it
-        __syncthreads();
-        C acc = 0;
-        for (int32_t i = tid; i < n; i += kSpmvThreads) {
-            const v2u q = qp[i];
-            const int64_t c0 = 4 * (int64_t)(q.x & kQuadIndexMask);
+    // what a block's first loads bring: lanes past the end read its first
+    // quad, row or value and ignore it (a block without quads reads the
+    // game's first)
+    const int64_t q0 = tab[0].e0;
+    v2u qd[NQ];
+    int32_t pr;
+    V dv;
+    auto fetch = [&](const SpmvBlock &bk, int32_t at, int32_t nd) __attribute__((always_inline)) {
+        const v2u *const qp = cp + (bk.n > 0 ? bk.e0 : q0);
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                C v, xv;
-                position(q.y, xin[c0 + k], k, v, xv);
-                acc = acc + v * xv;
-            }
+        for (int j = 0; j < NQ; ++j) {
+            const int32_t qi = j * kSpmvThreads + tid;
+            qd[j] = __builtin_nontemporal_load(qp + (qi < bk.n ? qi : 0));
         }
-        red[tid] = acc;
-        __syncthreads();
-        for (int w = kSpmvThreads / 2; w > 0; w >>= 1) {
-            if (tid < w) red[tid] = red[tid] + red[tid + w];
-            __syncthreads();
-        }
-        if (tid == 0) yout[rb] = (V)red[0];
-        return;
-    }
-    const int32_t pr = ptr[rb + (tid < nr ? tid : 0)];
-    if (n > 0) {
-        v2u qd[NQ];
+        pr = ptr[bk.row0 + (tid < bk.nr ? tid : 0)];
+        dv = dict[(int64_t)at * kCodes + (tid < nd ? tid : 0)];
+    };
+
+    SpmvBlock bk = tab[bid];
+    // (one game: its first block is the table's)
+    if (begin && bk.begin && tid == 0) begin_iteration_in<true>(sc + bk.slot);
+    int32_t nd = n_dict[bid];
+    fetch(bk, bid, nd);
+    int32_t nb = bid + step < last ? bid + step : bid;
+    SpmvBlock bn = tab[nb];
+    int32_t nn = n_dict[nb];
+    for (;;) {
+        const int32_t rb = bk.row0, nr = bk.nr, n = bk.n, p0 = bk.p0;
         V gx[NQ][4];
+        uint32_t code4[NQ];
 #pragma unroll
         for (int j = 0; j < NQ; ++j) {
-            const int32_t qi = j * kSpmvThreads + tid;
-            qd[j] = __builtin_nontemporal_load(qp + (qi < n ? qi : 0));
-        }
-#pragma unroll
-        for (int j = 0; j < NQ; ++j)
             load4_cached(xin + 4 * (int64_t)(qd[j].x & kQuadIndexMask), gx[j]);
-        __syncthreads();
+            code4[j] = qd[j].y;
+        }
+        const int64_t e0 = bk.e0;
+        const int32_t row = pr;
+        if (tid < nd) values[1 + tid] = (C)dv;
+        if (tid == 0) values[0] = (C)(-0.0);
+        // The next block's first loads, and the table entry after it.  They
+        // are issued in any case (past the end for the last block again): a
+        // branch here would have the waits for the gathers wait for them too.
+        const bool more = bid + step < last;
+        bid = nb;
+        bk = bn;
+        nd = nn;
+        fetch(bk, bid, nd);
+        nb = bid + step < last ? bid + step : bid;
+        bn = tab[nb];
+        nn = n_dict[nb];
+        __syncthreads();  // the values are there; the last block's sums are done
+        if (n > kCap) {
+            // a single long row, as spmv_blocks sums it
+            C acc = 0;
+            for (int32_t i = tid; i < n; i += kSpmvThreads) {
+                const v2u q = cp[e0 + i];
+                const int64_t c0 = 4 * (int64_t)(q.x & kQuadIndexMask);
 #pragma unroll
-        for (int j = 0; j < NQ; ++j) {
-            const int32_t qi = j * kSpmvThreads + tid;
-            if (SEQ) {
+                for (int k = 0; k < 4; ++k) {
+                    C v, xv;
+                    position(q.y, xin[c0 + k], k, v, xv);
+                    acc = acc + v * xv;
+                }
+            }
+            red[tid] = acc;
+            __syncthreads();
+            for (int w = kSpmvThreads / 2; w > 0; w >>= 1) {
+                if (tid < w) red[tid] = red[tid] + red[tid + w];
+                __syncthreads();
+            }
+            if (tid == 0) yout[rb] = (V)red[0];
+        } else {
+#pragma unroll
+            for (int j = 0; j < NQ; ++j) {
+                const int32_t qi = j * kSpmvThreads + tid;  // slots past the block are no row's
+                C qs = (C)(-0.0);
                 L o[4];
 #pragma unroll
                 for (int k = 0; k < 4; ++k) {
                     C v, xv;
-                    position(qd[j].y, gx[j][k], k, v, xv);
-                    o[k] = (L)(v * xv);
-                }
-                store4(&prod[4 * qi], o);  // slots past the block are no row's
-            } else {
-                C qs = (C)(-0.0);
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    C v, xv;
-                    position(qd[j].y, gx[j][k], k, v, xv);
-                    if constexpr (P == CFR_FP32_ACC64) qs = __builtin_fma(v, xv, qs);
+                    position(code4[j], gx[j][k], k, v, xv);
+                    if constexpr (SEQ) o[k] = (L)(v * xv);
+                    else if constexpr (P == CFR_FP32_ACC64) qs = __builtin_fma(v, xv, qs);
                     else qs = qs + v * xv;
                 }
-                prod[qi] = (L)qs;
+                if constexpr (SEQ) store4(&prod[4 * qi], o);
+                else prod[qi] = (L)qs;
+            }
+            if (tid < nr) s_ptr[tid] = per * (row - p0);
+            if (tid == 0) s_ptr[nr] = per * n;
+            __syncthreads();
+            if constexpr (SEQ) {
+                // whole quads, the next two on their way while two are added
+                if (tid < nr) {
+                    int32_t i = s_ptr[tid];
+                    const int32_t z = s_ptr[tid + 1];
+                    C acc = 0;
+                    L u[2][4];
+                    auto get = [&](int32_t at, L(&o)[4]) __attribute__((always_inline)) {
+                        load4_lds(&prod[at < z ? at : 0], o);
+                    };
+                    get(i, u[0]);
+                    get(i + 4, u[1]);
+                    while (i < z) {
+                        L t[2][4];
+                        get(i + 8, t[0]);
+                        get(i + 12, t[1]);
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) acc = acc + (C)u[0][k];
+                        if (i + 4 < z) {
+#pragma unroll
+                            for (int k = 0; k < 4; ++k) acc = acc + (C)u[1][k];
+                        }
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) {
+                            u[0][k] = t[0][k];
+                            u[1][k] = t[1][k];
+                        }
+                        i += 8;
+                    }
+                    yout[rb + tid] = (V)acc;
+                }
+            } else {
+                spmv_row_sums<P, SEQ>(prod, s_ptr, rb, nr, n, per, yout);
             }
         }
+        if (!more) return;
     }
-    constexpr int32_t per = SEQ ? 4 : 1;
-    if (tid < nr) s_ptr[tid] = per * (pr - p0);
-    if (tid == 0) s_ptr[nr] = per * n;
-    __syncthreads();
-    spmv_row_sums<P, SEQ>(prod, s_ptr, rb, nr, n, per, yout);
 }
 
 // ---------------------------------------------------------------------------
@@ -2520,7 +2606,11 @@ hipError_t spmv_coded_launch(const SpmvBlock *tab, int32_t n_tab, const int32_t 
                              hipStream_t st, hipEvent_t ev0, hipEvent_t ev1)
 {
     using V = typename Types<P>::V;
-    const unsigned grid = xcd_remap ? (unsigned)(((n_tab + 7) / 8) * 8) : (unsigned)n_tab;
+    // as many workgroups as the 256 compute units hold, with equal shares
+    constexpr int32_t kHeld = 256 * coded_blocks_per_cu(P, SEQ);
+    const int32_t share = (n_tab + kHeld - 1) / kHeld;
+    unsigned grid = (unsigned)((n_tab + share - 1) / share);
+    if (xcd_remap) grid = (grid + 7) / 8 * 8;
     if (ev0)
         hipExtLaunchKernelGGL((k_spmv_coded<P, SEQ, NQ>), dim3(grid), dim3(kSpmvThreads), 0, st, ev0,
                               ev1, 0u, n_tab, tab, ptr, (const uint2 *)code, (const V *)dict, n_dict,
