@@ -2453,14 +2453,32 @@ int Engine::evaluate_launch(const std::vector<int> &set, int kind, Scalars *out)
     }
     CHECK(spmv(*T, 0, src[1], dp[0].g, false, st, false));
     CHECK(spmv(*T, 1, src[0], dp[1].g, false, st, false));
+    BrTail tail{};
     for (int p = 0; p < 2; ++p) {
         const double usign = p == 0 ? 1.0 : -1.0;
-        for (int L = (int)T->up_level[p].size() - 1; L >= 0; --L) {
+        BrTail::Player &q = tail.pl[p];
+        q.tab = T->up[p];
+        q.root = T->root[p];
+        // levels from the root down that no game has more than kBrEntries
+        // entries of
+        while (q.levels < (int)T->up_level[p].size() && q.levels < kBrLevels) {
+            bool fits = true;
+            for (int k : set) {
+                const Slot &s = slots[(size_t)k];
+                if (q.levels < s.n_levels[p])
+                    fits &= s.lvl_inf[p][(size_t)q.levels + 1] - s.lvl_inf[p][(size_t)q.levels] <=
+                            kBrEntries * kRangeBlock;
+            }
+            if (!fits) break;
+            q.start[q.levels + 1] = q.start[q.levels] + T->up_level[p][(size_t)q.levels].second;
+            ++q.levels;
+        }
+        for (int L = (int)T->up_level[p].size() - 1; L >= q.levels; --L) {
             const auto &ul = T->up_level[p][(size_t)L];
             CHECK(launch_br(prec, T->up[p] + ul.first, ul.second, dp[p], usign, st));
         }
-        CHECK(launch_root_value(prec, T->root[p], T->n_root[p], dp[p], usign, sc, p, st));
     }
+    CHECK(launch_br_tail(prec, tail, T->n_root[0], dp[0], dp[1], sc, st));
     CHECK(launch_dot(prec, T->seq[0], T->n_seq[0], src[0], dp[0].g, partials, T->fin, T->n_fin,
                      sc, 2, st));
     CHECK(hipMemcpyAsync(out, sc, sizeof(Scalars) * slots.size(), hipMemcpyDeviceToHost, st));
@@ -2497,12 +2515,14 @@ int Engine::evaluate(const std::vector<int> &set, int kind)
 {
     if (set.empty()) return CFR_OK;
     HostTimer timer(&host_s[kHostEval], &host_n[kHostEval]);
-    std::vector<Scalars> h(slots.size());
-    int rc = evaluate_launch(set, kind, h.data());
+    // (eval_stage holds the results of a begun check until run_end)
+    std::vector<Scalars> h(eval_stage && !pending ? 0 : slots.size());
+    Scalars *out = h.empty() ? eval_stage : h.data();
+    int rc = evaluate_launch(set, kind, out);
     if (rc) return rc;
     rc = sync("evaluation");
     if (rc) return rc;
-    return evaluate_collect(set, h.data());
+    return evaluate_collect(set, out);
 }
 
 void Engine::apply_check(const std::vector<int> &set)

@@ -232,8 +232,22 @@ hipError_t launch_br(int prec, const RangeBlock *tab, int32_t n_tab, const DevPl
                      double usign, hipStream_t st);
 // Per game: usign*g[root] + sum of vinf over the root decision points,
 // into sc[slot].out[out_index].
-hipError_t launch_root_value(int prec, const SlotRef *tab, int32_t n_tab, const DevPlayer &p,
-                             double usign, Scalars *sc, int out_index, hipStream_t st);
+// The shallow levels of both players' max-sweeps over a set of games, and
+// their values at the empty sequence (Scalars::out[0] and [1]).  tab holds
+// the levels' entries one level after the other, level lv in [start[lv],
+// start[lv + 1]), at most kBrEntries of them a game and level; root one entry
+// a game.
+constexpr int kBrLevels = 24, kBrEntries = 4, kBrThreads = 1024;
+struct BrTail {
+    struct Player {
+        const RangeBlock *tab;
+        const SlotRef *root;
+        int32_t levels;
+        int32_t start[kBrLevels + 1];
+    } pl[2];
+};
+hipError_t launch_br_tail(int prec, const BrTail &t, int32_t n_games, const DevPlayer &p0,
+                          const DevPlayer &p1, Scalars *sc, hipStream_t st);
 // Per game: sum over its sequences of a[i]*b[i] in double, into
 // sc[slot].out[out_index] (partials: one double per entry of `tab`).
 hipError_t launch_dot(int prec, const RangeBlock *tab, int32_t n_tab, const void *a,

@@ -27,7 +27,9 @@
 //   k_fuse      the small levels below those in one launch, a block per
 //               group of whole subtrees from a host-built list.
 //   k_br        one level of the best-response max-sweep.
-//   k_normalize / k_root / k_dot   average normalisation and deterministic
+//   k_br_tail   its shallow levels and the value at the empty sequence, a
+//               workgroup per game and player.
+//   k_normalize / k_dot   average normalisation and deterministic
 //               per-game scalar reductions.  The per-iteration scalars (t,
 //               the averaging weight, the DCFR factors) of each game are
 //               advanced by that game's first block of the iteration's first
@@ -1741,6 +1743,24 @@ __global__ __launch_bounds__(kThreads) void k_export(const typename Types<P>::V 
     out[i - lo] = v;
 }
 
+// The best value of one decision point from its children's.
+template <int P>
+__device__ __forceinline__ typename Types<P>::C br_point(
+    int32_t j, const int32_t *__restrict__ inf_first, const int32_t *__restrict__ child_ptr,
+    const int32_t *__restrict__ child_idx, const typename Types<P>::V *__restrict__ g,
+    typename Types<P>::C usign, const typename Types<P>::C *vmax)
+{
+    using C = typename Types<P>::C;
+    const int32_t a0 = inf_first[j], a1 = inf_first[j + 1];
+    C best = 0;
+    for (int32_t a = a0; a < a1; ++a) {
+        const C acc =
+            child_sum<P>(usign * (C)g[a], child_ptr[a], child_ptr[a + 1], child_idx, vmax);
+        if (a == a0 || acc > best) best = acc;
+    }
+    return best;
+}
+
 template <int P>
 __global__ __launch_bounds__(kThreads) void k_br(const RangeBlock *__restrict__ tab,
                                                  const int32_t *__restrict__ inf_first,
@@ -1750,36 +1770,71 @@ __global__ __launch_bounds__(kThreads) void k_br(const RangeBlock *__restrict__ 
                                                  typename Types<P>::C usign,
                                                  typename Types<P>::C *__restrict__ vmax)
 {
-    using C = typename Types<P>::C;
     const RangeBlock rb = tab[blockIdx.x];
     const int32_t j = rb.lo + (int32_t)threadIdx.x;
     if (j >= rb.hi) return;
-    const int32_t a0 = inf_first[j], a1 = inf_first[j + 1];
-    C best = 0;
-    for (int32_t a = a0; a < a1; ++a) {
-        const C acc =
-            child_sum<P>(usign * (C)g[a], child_ptr[a], child_ptr[a + 1], child_idx, vmax);
-        if (a == a0 || acc > best) best = acc;
-    }
-    vmax[j] = best;
+    vmax[j] = br_point<P>(j, inf_first, child_ptr, child_idx, g, usign, vmax);
 }
 
-// value at each game's empty sequence: own utility there plus the values of
-// the decision points directly below it, summed in ascending order
+// The shallow levels of the max-sweep and the value at the empty sequence
+// (own utility there plus the values of the decision points directly below
+// it, in ascending order), one workgroup for each player of each game.  A
+// level of a game has at most kBrEntries table entries, so every level is one
+// round of the workgroup's threads, a barrier after it (2 us); a launch for
+// each level and player took 4 to 5.
 template <int P>
-__global__ __launch_bounds__(kThreads) void k_root(int32_t n_tab, const SlotRef *__restrict__ tab,
-                                                   const typename Types<P>::V *__restrict__ g,
-                                                   typename Types<P>::C usign,
-                                                   const typename Types<P>::C *__restrict__ v,
-                                                   Scalars *sc, int out_index)
+__global__ __launch_bounds__(kBrThreads) void k_br_tail(BrTail t, DevPlayer p0, DevPlayer p1,
+                                                        Scalars *sc)
 {
+    using V = typename Types<P>::V;
     using C = typename Types<P>::C;
-    const int32_t k = (int32_t)(blockIdx.x * kThreads + threadIdx.x);
-    if (k >= n_tab) return;
-    const SlotRef e = tab[k];
-    double acc = (double)(usign * (C)g[e.root]);
-    for (int32_t j = e.a; j < e.b; ++j) acc = acc + (double)v[j];
-    sc[e.slot].out[out_index] = acc;
+    __shared__ RangeBlock list[kBrLevels][kBrEntries];
+    __shared__ int32_t count[kBrLevels];
+    __shared__ double root[kBrThreads];
+    const int pl = (int)(blockIdx.x & 1);
+    const int tid = threadIdx.x;
+    const BrTail::Player &q = t.pl[pl];
+    const SlotRef ref = q.root[blockIdx.x >> 1];
+    const int32_t *const inf_first = pl ? p1.inf_first : p0.inf_first;
+    const int32_t *const child_ptr = pl ? p1.child_ptr : p0.child_ptr;
+    const int32_t *const child_idx = pl ? p1.child_idx : p0.child_idx;
+    const V *const g = (const V *)(pl ? p1.g : p0.g);
+    C *const vmax = (C *)(pl ? p1.vinf : p0.vinf);
+    const C usign = pl ? (C)-1 : (C)1;
+    if (tid < kBrLevels) count[tid] = 0;
+    __syncthreads();
+    // this game's entries, level by level
+    const int32_t n = q.start[q.levels];
+    for (int32_t e = tid; e < n; e += kBrThreads) {
+        const RangeBlock rb = q.tab[e];
+        if (rb.slot != ref.slot) continue;
+        int lv = 0;
+        while (q.start[lv + 1] <= e) ++lv;
+        const int at = atomicAdd(&count[lv], 1);
+        if (at < kBrEntries) list[lv][at] = rb;
+    }
+    __syncthreads();
+    for (int lv = q.levels - 1; lv >= 0; --lv) {
+        const int e = tid / kThreads;
+        if (e < count[lv]) {
+            const RangeBlock rb = list[lv][e];
+            const int32_t j = rb.lo + tid % kThreads;
+            if (j < rb.hi)
+                vmax[j] = br_point<P>(j, inf_first, child_ptr, child_idx, g, usign, vmax);
+        }
+        __syncthreads();
+    }
+    double acc = (double)(usign * (C)g[ref.root]);
+    for (int32_t j = ref.a; j < ref.b; j += kBrThreads) {
+        if (j + tid < ref.b) root[tid] = (double)vmax[j + tid];
+        __syncthreads();
+        if (tid == 0) {
+            const int m = ref.b - j < kBrThreads ? ref.b - j : kBrThreads;
+            for (int i = 0; i < m; ++i) acc = acc + root[i];
+        }
+        __syncthreads();
+    }
+    if (tid == 0) sc[ref.slot].out[pl] = acc;
 }
 
 // deterministic two-stage dot product in double: one partial per table
@@ -2410,14 +2465,12 @@ hipError_t br_t(const RangeBlock *tab, int32_t n_tab, const DevPlayer &p, double
 }
 
 template <int P>
-hipError_t root_t(const SlotRef *tab, int32_t n_tab, const DevPlayer &p, double usign,
-                  Scalars *sc, int out_index, hipStream_t st)
+hipError_t br_tail_t(const BrTail &t, int32_t n_games, const DevPlayer &p0, const DevPlayer &p1,
+                     Scalars *sc, hipStream_t st)
 {
-    using T = Types<P>;
-    if (n_tab <= 0) return hipSuccess;
-    hipLaunchKernelGGL((k_root<P>), dim3(grid_for(n_tab)), dim3(kThreads), 0, st, n_tab, tab,
-                       (const typename T::V *)p.g, (typename T::C)usign,
-                       (const typename T::C *)p.vinf, sc, out_index);
+    if (n_games <= 0) return hipSuccess;
+    hipLaunchKernelGGL((k_br_tail<P>), dim3(2 * (unsigned)n_games), dim3(kBrThreads), 0, st, t, p0,
+                       p1, sc);
     return hipGetLastError();
 }
 
@@ -2520,10 +2573,10 @@ hipError_t launch_br(int prec, const RangeBlock *tab, int32_t n_tab, const DevPl
     CFR_DISPATCH(prec, br_t<P>(tab, n_tab, p, usign, st));
 }
 
-hipError_t launch_root_value(int prec, const SlotRef *tab, int32_t n_tab, const DevPlayer &p,
-                             double usign, Scalars *sc, int out_index, hipStream_t st)
+hipError_t launch_br_tail(int prec, const BrTail &t, int32_t n_games, const DevPlayer &p0,
+                          const DevPlayer &p1, Scalars *sc, hipStream_t st)
 {
-    CFR_DISPATCH(prec, root_t<P>(tab, n_tab, p, usign, sc, out_index, st));
+    CFR_DISPATCH(prec, br_tail_t<P>(t, n_games, p0, p1, sc, st));
 }
 
 hipError_t launch_dot(int prec, const RangeBlock *tab, int32_t n_tab, const void *a,
