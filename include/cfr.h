@@ -273,6 +273,18 @@ int cfr_kernel_timing(cfr_solver *s, int enable);
 int cfr_kernel_stats(cfr_solver *s, int kernel, int64_t *launches, double *total_ms,
                      double *bytes_per_launch);
 
+/* How the iterations run (see use_graph), CFR_RESIDENT_STATS values: [0] -1
+ * not decided since the tiling or the set of games changed, 0 a launch per
+ * step, 1 whole iterations inside one launch; [1] such launches so far; [2]
+ * games and [3] workgroups of the next one; [4] games set up for it so far;
+ * [5] device bytes held for it; [6] page-locked stagings allocated for
+ * downloads so far; and of this game, once set up, [7] its workgroups, [8],
+ * [9] each player's levels that all of them hold, [10] 1 when its averages
+ * stay in device memory, [11], [12] 1 when that product reads quads, [13]
+ * the estimate of one iteration (ns).  For reports; does not wait.         */
+#define CFR_RESIDENT_STATS 14
+int cfr_resident_stats(cfr_solver *s, int64_t *out);
+
 /* Checkpointing.  The state of a solver — iteration counter, averaging
  * weights, and per player the cumulative regrets, predictions, average
  * accumulators and current behavioural and sequence-form strategies — as
@@ -522,6 +534,9 @@ int cfr_batch_kernel_stats(cfr_batch *b, int kernel, int64_t *launches, double *
  * and copies of prepared quads, part of the additions); out[7..13] the
  * matching call counts.  For reports.                                     */
 int cfr_batch_host_stats(cfr_batch *b, double *out);
+
+/* As cfr_resident_stats, with one game's own entries.                     */
+int cfr_batch_resident_stats(cfr_batch *b, int64_t id, int64_t *out);
 
 int cfr_batch_destroy(cfr_batch *b);
 

@@ -105,6 +105,8 @@ _lib.cfr_iteration.argtypes = [C.c_void_p, _P(C.c_int64)]
 _lib.cfr_kernel_timing.argtypes = [C.c_void_p, C.c_int]
 _lib.cfr_kernel_stats.argtypes = [C.c_void_p, C.c_int, _P(C.c_int64), _P(C.c_double),
                                   _P(C.c_double)]
+_lib.cfr_resident_stats.argtypes = [C.c_void_p, _P(C.c_int64)]
+_lib.cfr_batch_resident_stats.argtypes = [C.c_void_p, C.c_int64, _P(C.c_int64)]
 _lib.cfr_state_size.argtypes = [C.c_void_p, _P(C.c_size_t)]
 _lib.cfr_get_state.argtypes = [C.c_void_p, C.c_void_p, C.c_size_t]
 _lib.cfr_set_state.argtypes = [C.c_void_p, C.c_void_p, C.c_size_t]
@@ -158,7 +160,8 @@ for _f in ("cfr_options_default", "cfr_validate", "cfr_workspace_size", "cfr_cre
            "cfr_batch_set_tiling", "cfr_batch_tune", "cfr_batch_kernel_timing",
            "cfr_batch_kernel_stats", "cfr_batch_destroy", "cfr_prepare", "cfr_prepared_size",
            "cfr_batch_add_prepared", "cfr_prepared_destroy", "cfr_batch_host_stats",
-           "cfr_prepare_quads", "cfr_batch_index_limits"):
+           "cfr_prepare_quads", "cfr_batch_index_limits", "cfr_resident_stats",
+           "cfr_batch_resident_stats"):
     getattr(_lib, _f).restype = C.c_int
 
 
@@ -291,6 +294,20 @@ def cfr_kernel_stats(h, kernel: int):
     _check(_lib.cfr_kernel_stats(h, kernel, C.byref(n), C.byref(ms), C.byref(by)),
            "cfr_kernel_stats")
     return int(n.value), float(ms.value), float(by.value)
+
+
+RESIDENT_STATS = ("state", "launches", "teams", "workgroups", "setups", "device_bytes",
+                  "stagings", "blocks", "cut0", "cut1", "lean", "quads0", "quads1", "cost_ns")
+
+
+def _resident_dict(out) -> dict:
+    return {k: int(out[i]) for i, k in enumerate(RESIDENT_STATS)}
+
+
+def cfr_resident_stats(h) -> dict:
+    out = (C.c_int64 * len(RESIDENT_STATS))()
+    _check(_lib.cfr_resident_stats(h, out), "cfr_resident_stats")
+    return _resident_dict(out)
 
 
 def cfr_get_state(h) -> bytes:
@@ -478,6 +495,12 @@ def cfr_batch_host_stats(h) -> dict:
             for i, k in enumerate(HOST_STATS)}
 
 
+def cfr_batch_resident_stats(h, gid: int) -> dict:
+    out = (C.c_int64 * len(RESIDENT_STATS))()
+    _check(_lib.cfr_batch_resident_stats(h, int(gid), out), "cfr_batch_resident_stats")
+    return _resident_dict(out)
+
+
 def cfr_batch_destroy(h):
     _check(_lib.cfr_batch_destroy(h), "cfr_batch_destroy")
 
@@ -570,6 +593,10 @@ class Solver:
 
     def kernel_stats(self, kernel: int):
         return cfr_kernel_stats(self.h, kernel)
+
+    def resident_stats(self) -> dict:
+        """How the iterations run (cfr_resident_stats)."""
+        return cfr_resident_stats(self.h)
 
     def get_state(self) -> bytes:
         """Checkpoint image of the solver's state (see cfr_get_state)."""
@@ -724,6 +751,9 @@ class Batch:
 
     def host_stats(self) -> dict:
         return cfr_batch_host_stats(self.h)
+
+    def resident_stats(self, gid: int) -> dict:
+        return cfr_batch_resident_stats(self.h, gid)
 
     def kernel_stats(self, kernel: int):
         return cfr_batch_kernel_stats(self.h, kernel)

@@ -814,6 +814,13 @@ int cfr_kernel_stats(cfr_solver *s, int kernel, int64_t *launches, double *total
     return kernel_stats(s->eng, kernel, launches, total_ms, bytes_per_launch);
 }
 
+int cfr_resident_stats(cfr_solver *s, int64_t *out)
+{
+    if (!s || !out) return fail(CFR_EINVAL, "null argument");
+    s->eng.resident_stats(0, out);
+    return CFR_OK;
+}
+
 int cfr_get_tiling(cfr_solver *s, cfr_spmv_tiling *t)
 {
     if (!s || !t) return fail(CFR_EINVAL, "null argument");
@@ -1338,6 +1345,15 @@ int cfr_batch_host_stats(cfr_batch *b, double *out)
         out[i] = b->eng.host_s[i];
         out[cfr::Engine::kHostN + i] = (double)b->eng.host_n[i];
     }
+    return CFR_OK;
+}
+
+int cfr_batch_resident_stats(cfr_batch *b, int64_t id, int64_t *out)
+{
+    if (!b || !out) return fail(CFR_EINVAL, "null argument");
+    const int k = b->find(id);
+    if (k < 0) return fail(CFR_EINVAL, "unknown game");
+    b->eng.resident_stats(k, out);
     return CFR_OK;
 }
 

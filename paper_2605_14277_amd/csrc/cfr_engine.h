@@ -364,6 +364,7 @@ struct Engine {
     int res_threads = 0;
     double res_asked = 0;  // iterations asked for while the loop was not set up
     bool res_coop = false;
+    int64_t res_launches = 0, res_setups = 0, exp_allocs = 0;  // for reports
 
     // per-launch timing of the payoff products (HIP events on st)
     bool timing = false;
@@ -439,6 +440,8 @@ struct Engine {
     void drop_resident(Slot &s);
     // The failure mark of a game's scalars, as copied back.
     int check_mark(const Scalars &h);
+    // What cfr_resident_stats reports, game `slot`'s own entries with it.
+    void resident_stats(int slot, int64_t *out) const;
     // Evaluates the average (or current) profile of the games in `set`;
     // results land in each slot's `last`.
     int evaluate(const std::vector<int> &set, int kind);

@@ -2181,6 +2181,7 @@ int Engine::build_resident(int k, int max_blocks)
     const size_t o_bar = take(4 * (size_t)kResBarWords);
     plan->dev = device_buffer(at);
     if (!plan->dev) return CFR_OK;  // the launch-per-step path needs no copy
+    plan->dev_bytes = at;
     char *D = plan->dev.get();
     std::vector<char> h(host_bytes, 0);
     auto put = [&h](size_t o, const void *src, size_t bytes) {
@@ -2238,7 +2239,28 @@ int Engine::build_resident(int k, int max_blocks)
     plan->local[0] = plan->local[1] = {};
     plan->n_seq = s.n_seq[0] + s.n_seq[1];
     s.res = plan;
+    ++res_setups;
     return CFR_OK;
+}
+
+void Engine::resident_stats(int k, int64_t *out) const
+{
+    const Slot &s = slots[(size_t)k];
+    int64_t teams = 0, blocks = 0, bytes = (int64_t)res_dev_bytes;
+    for (const Slot &q : slots) {
+        if (!q.res) continue;
+        bytes += (int64_t)q.res->dev_bytes;
+        if (resident != 1 || !q.active) continue;
+        ++teams;
+        blocks += q.res->blocks;
+    }
+    const ResidentPlan *pl = s.res.get();
+    const int64_t v[CFR_RESIDENT_STATS] = {
+        resident, res_launches, teams, blocks, res_setups, bytes, exp_allocs,
+        pl ? pl->blocks : 0, pl ? pl->sh[0].c : 0, pl ? pl->sh[1].c : 0, pl ? pl->team.lean : 0,
+        pl ? pl->team.quads[0] : 0, pl ? pl->team.quads[1] : 0,
+        pl ? (int64_t)(1e3 * pl->cost_us) : 0};
+    std::copy(v, v + CFR_RESIDENT_STATS, out);
 }
 
 int Engine::setup_resident(const std::vector<int> &act)
@@ -2389,6 +2411,7 @@ int Engine::iterate(int64_t n)
                                     dp[0], dp[1], st);
             if (e != hipSuccess) return device_error("iteration launch", e);
             res_ran = true;
+            res_launches += (n + kResLaunchIterations - 1) / kResLaunchIterations;
             for (int k : act) slots[(size_t)k].t += n;
             return CFR_OK;
         }
@@ -2690,6 +2713,7 @@ bool Engine::export_ready(int32_t n)
     }
     exp_stage = (char *)p;
     exp_part = part;
+    ++exp_allocs;
     return true;
 }
 

@@ -189,6 +189,7 @@ struct ResidentPlan {
     std::vector<int32_t> local[2];  // one workgroup: local sequence of each of the game's
     // device memory: everything above, the streams and the exchange arrays
     std::shared_ptr<char> dev;
+    size_t dev_bytes = 0;
     ResTeam team;
 };
 
