@@ -431,6 +431,8 @@ struct Engine {
     hipError_t sweeps(const Tables &T, int p, double usign, hipStream_t s, bool *fold = nullptr);
     hipError_t enqueue_iteration(hipStream_t s);
     hipError_t build_graph();
+    // The stream is being captured: only launches may be enqueued on it.
+    bool capturing() const;
     // n iterations of every active game (no checks).
     int iterate(int64_t n);
     // Decides on the resident loop for the iterating games and sets up its

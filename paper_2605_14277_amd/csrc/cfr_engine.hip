@@ -2370,6 +2370,14 @@ int Engine::setup_resident(const std::vector<int> &act)
     return CFR_OK;
 }
 
+bool Engine::capturing() const
+{
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &cs) == hipSuccess) return cs != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();  // a capture elsewhere that this stream may not disturb
+    return true;
+}
+
 int Engine::iterate(int64_t n)
 {
     if (n <= 0) return CFR_OK;
@@ -2385,7 +2393,8 @@ int Engine::iterate(int64_t n)
         if (slots[(size_t)k].gp.variant < CFR_VANILLA)
             return fail(CFR_ESTATE, "a game has no regret minimiser set");
     hipError_t e = hipSuccess;
-    if (n >= kResMinIterations) {
+    // (a set-up allocates and waits, which would end a capture)
+    if (n >= kResMinIterations && !timing && !capturing()) {
         if (resident < 0) {
             // planning, the streams' copy and their memory are paid once: by
             // as many iterations as they save
@@ -2401,9 +2410,7 @@ int Engine::iterate(int64_t n)
                 if (rc) return rc;
             }
         }
-        hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-        if (resident == 1 && !timing &&
-            hipStreamIsCapturing(st, &cs) == hipSuccess && cs == hipStreamCaptureStatusNone) {
+        if (resident == 1) {
             HostTimer timer(&host_s[kHostEnqueue], &host_n[kHostEnqueue]);
             for (int64_t i = 0; i < n && e == hipSuccess; i += kResLaunchIterations)
                 e = launch_resident(prec, res_teams, res_map, res_grid, res_lds, res_threads, res_coop,
@@ -2686,13 +2693,7 @@ int Engine::time_spmv(int which, int reps, double *ms)
 // Room for parts of n sequences (at most kExportPart); false: use plain copies.
 bool Engine::export_ready(int32_t n)
 {
-    if (no_alloc) return false;
-    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(st, &cs) != hipSuccess) {
-        (void)hipGetLastError();
-        return false;
-    }
-    if (cs != hipStreamCaptureStatusNone) return false;
+    if (no_alloc || capturing()) return false;
     for (hipEvent_t &ev_ : exp_ev)
         if (!ev_ && hipEventCreateWithFlags(&ev_, hipEventDisableTiming) != hipSuccess) {
             ev_ = nullptr;
