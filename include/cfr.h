@@ -281,8 +281,10 @@ int cfr_kernel_stats(cfr_solver *s, int kernel, int64_t *launches, double *total
  * downloads so far; and of this game, once set up, [7] its workgroups, [8],
  * [9] each player's levels that all of them hold, [10] 1 when its averages
  * stay in device memory, [11], [12] 1 when that product reads quads, [13]
- * the estimate of one iteration (ns).  For reports; does not wait.         */
-#define CFR_RESIDENT_STATS 14
+ * the estimate of one iteration (ns); [14] the most workgroups that the
+ * device and the stream's compute-unit mask allow one game.  For reports;
+ * does not wait.                                                           */
+#define CFR_RESIDENT_STATS 15
 int cfr_resident_stats(cfr_solver *s, int64_t *out);
 
 /* Checkpointing.  The state of a solver — iteration counter, averaging

@@ -297,7 +297,8 @@ def cfr_kernel_stats(h, kernel: int):
 
 
 RESIDENT_STATS = ("state", "launches", "teams", "workgroups", "setups", "device_bytes",
-                  "stagings", "blocks", "cut0", "cut1", "lean", "quads0", "quads1", "cost_ns")
+                  "stagings", "blocks", "cut0", "cut1", "lean", "quads0", "quads1", "cost_ns",
+                  "units")
 
 
 def _resident_dict(out) -> dict:

@@ -354,6 +354,8 @@ struct Engine {
     // The resident loop over the iterating games: -1 not decided since their
     // set or tiling changed, 0 not used, 1 its teams are set up.
     int resident = -1;
+    int res_units = 1;         // workgroups of a team at most (team_units)
+    bool res_refused = false;  // a launch of it was refused: not used again
     bool res_ran = false;  // some launch of it was enqueued (its failure mark is read back)
     char *res_dev = nullptr;  // teams and workgroup map
     size_t res_dev_bytes = 0;

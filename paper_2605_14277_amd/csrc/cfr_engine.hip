@@ -902,6 +902,28 @@ int64_t RangeAlloc::largest() const
 // Engine
 // ---------------------------------------------------------------------------
 
+// Workgroups that a team of the resident loop may have on this device and
+// stream, all of them on the chip at once at one a compute unit: a multiple of
+// eight (they are dealt round over the XCDs).  1 (teams without barriers)
+// where the device launches nothing cooperatively or a compute-unit mask
+// leaves the stream a part of it.
+static int team_units(int dev, hipStream_t st)
+{
+    int units = 0, together = 0;
+    uint32_t mask[32] = {};
+    // (the named streams 1 and 2 are no handles, and have no mask of their own)
+    const hipStream_t of = (uintptr_t)st > 2 ? st : nullptr;
+    if (hipDeviceGetAttribute(&units, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+        hipDeviceGetAttribute(&together, hipDeviceAttributeCooperativeLaunch, dev) != hipSuccess ||
+        hipExtStreamGetCUMask(of, 32, mask) != hipSuccess) {
+        (void)hipGetLastError();
+        return 1;
+    }
+    int open = 0;
+    for (uint32_t w : mask) open += __builtin_popcount(w);
+    return together && open >= units ? std::max(1, std::min(units, kResCus) / kResXcds * kResXcds) : 1;
+}
+
 int Engine::init(const Capacity &c, int precision, int dev, hipStream_t stream, void *workspace,
                  size_t workspace_bytes)
 {
@@ -966,6 +988,7 @@ int Engine::init(const Capacity &c, int precision, int dev, hipStream_t stream, 
         e = hipMemsetAsync(dp[p].child_idx, 0, 4 * (size_t)std::max<int64_t>(c.inf[p], 1), st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);
     if (e != hipSuccess) return device_error("workspace initialisation", e);
+    res_units = team_units(device, st);
     // an allocation-free engine admits its one game synchronously on the
     // caller's stream and stages from ordinary host memory
     if (no_alloc) return init_arenas(c);
@@ -2259,21 +2282,21 @@ void Engine::resident_stats(int k, int64_t *out) const
         resident, res_launches, teams, blocks, res_setups, bytes, exp_allocs,
         pl ? pl->blocks : 0, pl ? pl->sh[0].c : 0, pl ? pl->sh[1].c : 0, pl ? pl->team.lean : 0,
         pl ? pl->team.quads[0] : 0, pl ? pl->team.quads[1] : 0,
-        pl ? (int64_t)(1e3 * pl->cost_us) : 0};
+        pl ? (int64_t)(1e3 * pl->cost_us) : 0, res_units};
     std::copy(v, v + CFR_RESIDENT_STATS, out);
 }
 
 int Engine::setup_resident(const std::vector<int> &act)
 {
     resident = 0;
-    if (no_alloc || !use_graph || async_admission || down_pass != CFR_DOWN_DEFAULT ||
+    if (no_alloc || res_refused || !use_graph || async_admission || down_pass != CFR_DOWN_DEFAULT ||
         up_pass != CFR_UP_DEFAULT || act.empty() || act.size() > (size_t)kResTeamsMax)
         return CFR_OK;
     // a workgroup's LDS holds some 2,500 sequences
     auto need = [&](const Slot &s) { return (s.n_seq[0] + s.n_seq[1]) / 2500 + 1; };
     auto load = [&](const Slot &s) { return (double)s.nnz + 8.0 * (s.n_seq[0] + s.n_seq[1]); };
     double total = 0;
-    int64_t spare = kResCus;
+    int64_t spare = res_units;
     for (int k : act) {
         const Slot &s = slots[(size_t)k];
         if (!s.res_src || std::max(s.n_levels[0], s.n_levels[1]) > kDownAllMaxDepth) return CFR_OK;
@@ -2290,8 +2313,9 @@ int Engine::setup_resident(const std::vector<int> &act)
         for (int k : act) {
             Slot &s = slots[(size_t)k];
             const int most = act.size() == 1
-                                 ? kResCus
-                                 : (int)(need(s) + load(s) / total * (double)spare);
+                                 ? res_units
+                                 : (int)std::min<double>(
+                                       res_units, (double)need(s) + load(s) / total * (double)spare);
             if (s.res_tried == 0 || (attempt && s.res_tried != most)) {
                 int rc = build_resident(k, most);
                 if (rc) return rc;
@@ -2309,8 +2333,9 @@ int Engine::setup_resident(const std::vector<int> &act)
         }
         // teams with barriers have to be resident all together, one
         // workgroup per compute unit
-        if (many && blocks > kResCus) continue;
+        if (many && blocks > res_units) continue;
         // workgroup i runs on XCD i % 8: teams of at most 32 on one XCD
+        const size_t lane_units = (size_t)std::max(1, res_units / kResXcds);
         std::vector<int> order(act);
         std::stable_sort(order.begin(), order.end(), [&](int a, int b) {
             return slots[(size_t)a].res->blocks > slots[(size_t)b].res->blocks;
@@ -2329,7 +2354,7 @@ int Engine::setup_resident(const std::vector<int> &act)
             for (int i = 1; i < kResXcds; ++i)
                 if (lane[i].size() < lane[x].size()) x = i;
             const bool one = pl.blocks <= kResXcdCus &&
-                             (!many || lane[x].size() + (size_t)pl.blocks <= (size_t)kResXcdCus);
+                             (!many || lane[x].size() + (size_t)pl.blocks <= lane_units);
             for (int32_t r = 0; r < pl.blocks; ++r) {
                 if (!one && r > 0)
                     for (int i = x = 0; i < kResXcds; ++i)
@@ -2339,6 +2364,7 @@ int Engine::setup_resident(const std::vector<int> &act)
         }
         size_t depth = 0;
         for (auto &l : lane) depth = std::max(depth, l.size());
+        if (many && depth > lane_units) return CFR_OK;  // (the whole grid has to fit)
         std::vector<int32_t> map(depth * kResXcds, -1);
         for (int x = 0; x < kResXcds; ++x)
             for (size_t i = 0; i < lane[x].size(); ++i) map[i * kResXcds + (size_t)x] = lane[x][i];
@@ -2412,15 +2438,25 @@ int Engine::iterate(int64_t n)
         }
         if (resident == 1) {
             HostTimer timer(&host_s[kHostEnqueue], &host_n[kHostEnqueue]);
-            for (int64_t i = 0; i < n && e == hipSuccess; i += kResLaunchIterations)
+            int64_t i = 0;
+            for (; i < n; i += kResLaunchIterations) {
                 e = launch_resident(prec, res_teams, res_map, res_grid, res_lds, res_threads, res_coop,
                                     (int)std::min<int64_t>(kResLaunchIterations, n - i), mode, sc,
                                     dp[0], dp[1], st);
-            if (e != hipSuccess) return device_error("iteration launch", e);
-            res_ran = true;
-            res_launches += (n + kResLaunchIterations - 1) / kResLaunchIterations;
-            for (int k : act) slots[(size_t)k].t += n;
-            return CFR_OK;
+                if (e != hipSuccess) break;
+                ++res_launches;
+            }
+            if (e != hipSuccess && i > 0) return device_error("iteration launch", e);
+            if (e == hipSuccess) {
+                res_ran = true;
+                for (int k : act) slots[(size_t)k].t += n;
+                return CFR_OK;
+            }
+            // refused before anything ran: a launch per step, from here on
+            (void)hipGetLastError();
+            e = hipSuccess;
+            res_refused = true;
+            resident = 0;
         }
     }
     // Capturing and instantiating the iteration's graph costs about as much

@@ -34,7 +34,7 @@ constexpr int kResWavesMax = kResThreadsMax / 64;
 // players'): a barrier over 16 waves costs more than they bring.
 constexpr int32_t kResFewSeq = 512;
 constexpr int kResXcds = 8;
-constexpr int kResCus = 256;              // workgroups of a team at most: one per compute unit
+constexpr int kResCus = 256;              // workgroups of a team at most (fewer on a smaller device)
 constexpr int kResXcdCus = 32;            // a team up to this size stays on one XCD
 constexpr uint32_t kResLds = 156 * 1024;  // LDS one workgroup may take
 constexpr int kResBarWords = 1024;        // counters of one team (u32)
