@@ -751,8 +751,20 @@ int cfr_set_state(cfr_solver *s, const void *in, size_t len)
     DeviceGuard guard(e.device);
     const char *o = (const char *)in + sizeof h;
     const size_t R = cfr::accum_bytes(e.prec), V = cfr::value_bytes(e.prec);
+    // a failure that no read-back has reported yet must not be written over
+    cfr::Scalars now{}, scal;
+    hipError_t err = hipSuccess;
+    if (e.res_ran) {
+        err = hipMemcpyAsync(&now, e.sc, sizeof now, hipMemcpyDeviceToHost, e.st);
+        if (err != hipSuccess) return e.device_error("state copy", err);
+        int rc = e.sync("state copy");
+        if (!rc) rc = e.check_mark(now);
+        if (rc) return rc;
+    }
     // the scalars carry the variant and constants the image was taken with
-    hipError_t err = hipMemcpyAsync(e.sc, o, sizeof(cfr::Scalars), hipMemcpyHostToDevice, e.st);
+    std::memcpy(&scal, o, sizeof scal);
+    scal.pad[0] = scal.pad[1] = 0;
+    err = hipMemcpyAsync(e.sc, &scal, sizeof scal, hipMemcpyHostToDevice, e.st);
     o += sizeof(cfr::Scalars);
     for (int p = 0; p < 2 && err == hipSuccess; ++p) {
         const size_t n = (size_t)sl.n_seq[p], S = (size_t)sl.sb[p];
@@ -766,18 +778,16 @@ int cfr_set_state(cfr_solver *s, const void *in, size_t len)
         }
     }
     if (err != hipSuccess) return e.device_error("state copy", err);
-    int rc = e.sync("state copy");
+    const int rc = e.sync("state copy");
     if (rc) return rc;
     sl.t = h.t;
     if (h.variant >= 0) {
-        cfr::Scalars sc;
-        std::memcpy(&sc, (const char *)in + sizeof h, sizeof sc);
         cfr::GameParams gp = sl.gp;
         gp.variant = h.variant;
-        gp.avg_kind = sc.avg_kind;
-        gp.alpha = sc.alpha;
-        gp.beta = sc.beta;
-        gp.gamma = sc.gamma;
+        gp.avg_kind = scal.avg_kind;
+        gp.alpha = scal.alpha;
+        gp.beta = scal.beta;
+        gp.gamma = scal.gamma;
         sl.gp = gp;
         s->variant = h.variant;
         s->mode = h.mode;

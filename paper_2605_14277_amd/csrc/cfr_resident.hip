@@ -554,9 +554,13 @@ __global__ __launch_bounds__(NT) void k_resident(const ResTeam *__restrict__ tea
     if (tid == 0) {
         ls->t = gs->t;
         ls->W = gs->W;
-        ls->ok = 1;
+        // a team that has failed stays so: its counters hold what was left of
+        // the launch that did, and no later wait on them means anything
+        ls->ok = bar.n > 1 && ag_load(bar.c + 16) ? 0 : 1;
+        if (!ls->ok) *bar.mark = 1;
     }
     __syncthreads();
+    if (!ls->ok) return;
 
     // Where the gatherers of a player's strategy read it.
     auto target = [&](int p) __attribute__((always_inline)) {
