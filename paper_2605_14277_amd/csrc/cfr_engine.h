@@ -226,7 +226,7 @@ struct Slot {
     // tiling (null: not made, or none fits)
     std::shared_ptr<ResSource> res_src;
     std::shared_ptr<ResidentPlan> res;
-    int res_tried = 0;  // most workgroups a plan was sought for
+    int res_none = 0;  // most workgroups that a plan was sought for in vain
     double last[5] = {0, 0, 0, 0, 0};    // last evaluation: expl, NashConv, BR1, BR2, value
     // asynchronous admission: host copies the uploads read, and the event
     // that marks their completion on the upload stream
@@ -438,9 +438,12 @@ struct Engine {
     // n iterations of every active game (no checks).
     int iterate(int64_t n);
     // Decides on the resident loop for the iterating games and sets up its
-    // teams (plans are kept with the games).
-    int setup_resident(const std::vector<int> &act);
-    int build_resident(int slot, int max_blocks);
+    // teams (kept with the games while they are used).
+    int setup_resident(const std::vector<int> &act, bool wider);
+    // A game's plan for at most `most` workgroups (host only; null: none
+    // fits), and its device memory (none had: plan->dev stays null).
+    std::shared_ptr<ResidentPlan> plan_team(int slot, int most);
+    int fill_team(int slot, const std::shared_ptr<ResidentPlan> &plan);
     void drop_resident(Slot &s);
     // The failure mark of a game's scalars, as copied back.
     int check_mark(const Scalars &h);

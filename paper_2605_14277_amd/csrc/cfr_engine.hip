@@ -1377,7 +1377,7 @@ int Engine::set_perm(int which, int on)
 void Engine::drop_resident(Slot &s)
 {
     s.res.reset();
-    s.res_tried = 0;
+    s.res_none = 0;
     resident = -1;
 }
 
@@ -2151,12 +2151,11 @@ static std::shared_ptr<char> device_buffer(size_t bytes)
     return std::shared_ptr<char>((char *)p, [](char *q) { (void)hipFree(q); });
 }
 
-int Engine::build_resident(int k, int max_blocks)
+std::shared_ptr<ResidentPlan> Engine::plan_team(int k, int most)
 {
-    Slot &s = slots[(size_t)k];
-    s.res_tried = max_blocks;
-    s.res.reset();
+    const Slot &s = slots[(size_t)k];
     auto plan = std::make_shared<ResidentPlan>();
+    plan->most = most;
     ResTeam &T = plan->team;
     T = ResTeam{};
     ResRows rows[2];
@@ -2167,7 +2166,7 @@ int Engine::build_resident(int k, int max_blocks)
         rows[w].lr.assign((size_t)s.n_seq[w], 0);
         for (const SpmvBlock &b : s.blocks[w]) {
             // a row longer than a block is summed by a tree over a block
-            if (b.n > spmv_block_cap_v(items[w], vec[w])) return CFR_OK;
+            if (b.n > spmv_block_cap_v(items[w], vec[w])) return nullptr;
             if (sequential()) continue;
             // the lanes k_spmv gives each row of this block
             int lanes = 64, lr = 6;
@@ -2177,7 +2176,15 @@ int Engine::build_resident(int k, int max_blocks)
                 rows[w].lr[(size_t)(b.row0 - s.sb[w] + r)] = (uint8_t)lr;
         }
     }
-    if (!plan_resident(*s.res_src, rows, s.sb, prec, max_blocks, *plan)) return CFR_OK;
+    if (!plan_resident(*s.res_src, rows, s.sb, prec, most, *plan)) return nullptr;
+    plan->n_seq = s.n_seq[0] + s.n_seq[1];
+    return plan;
+}
+
+int Engine::fill_team(int k, const std::shared_ptr<ResidentPlan> &plan)
+{
+    Slot &s = slots[(size_t)k];
+    ResTeam &T = plan->team;
     const size_t V = value_bytes(prec), C = compute_bytes(prec);
     size_t at = 0;
     auto take = [&at](size_t bytes) {
@@ -2260,7 +2267,6 @@ int Engine::build_resident(int k, int max_blocks)
     plan->row = {};
     plan->src = {};
     plan->local[0] = plan->local[1] = {};
-    plan->n_seq = s.n_seq[0] + s.n_seq[1];
     s.res = plan;
     ++res_setups;
     return CFR_OK;
@@ -2286,70 +2292,105 @@ void Engine::resident_stats(int k, int64_t *out) const
     std::copy(v, v + CFR_RESIDENT_STATS, out);
 }
 
-int Engine::setup_resident(const std::vector<int> &act)
+int Engine::setup_resident(const std::vector<int> &act, bool wider)
 {
+    // plans that stay unused are not kept: they hold copies of the streams
+    auto unused = [&] {
+        bool any = false;
+        for (int k : act) any = any || slots[(size_t)k].res;
+        if (any) (void)hipStreamSynchronize(st);  // launches may still read them
+        for (int k : act) slots[(size_t)k].res.reset();
+        return CFR_OK;
+    };
     resident = 0;
     if (no_alloc || res_refused || !use_graph || async_admission || down_pass != CFR_DOWN_DEFAULT ||
         up_pass != CFR_UP_DEFAULT || act.empty() || act.size() > (size_t)kResTeamsMax)
-        return CFR_OK;
+        return unused();
+    const bool alone = act.size() == 1;
     // a workgroup's LDS holds some 2,500 sequences
     auto need = [&](const Slot &s) { return (s.n_seq[0] + s.n_seq[1]) / 2500 + 1; };
     auto load = [&](const Slot &s) { return (double)s.nnz + 8.0 * (s.n_seq[0] + s.n_seq[1]); };
-    double total = 0;
-    int64_t spare = res_units;
+    double total = 0, seqs = 0;
+    int64_t spare = res_units, least = 0;
+    bool several = false;
     for (int k : act) {
         const Slot &s = slots[(size_t)k];
-        if (!s.res_src || std::max(s.n_levels[0], s.n_levels[1]) > kDownAllMaxDepth) return CFR_OK;
+        if (!s.res_src || std::max(s.n_levels[0], s.n_levels[1]) > kDownAllMaxDepth) return unused();
+        const int64_t n = (int64_t)s.n_seq[0] + s.n_seq[1], b = res_least_blocks(n, prec);
         total += load(s);
+        seqs += (double)n;
         spare -= need(s);
+        least += b;
+        several = several || b > 1;
     }
+    if (several && least > res_units) return unused();  // no plans fit together
     spare = std::max<int64_t>(spare, 0);
     HostTimer timer(&host_s[kHostTables], &host_n[kHostTables]);
     // each game's share of the compute units; plans made for another set are
-    // kept while all teams fit
+    // kept while all teams fit, unless a game left alone is to have a wider
+    // one.  Nothing of a plan is put on the device before all are known to fit.
+    std::vector<std::shared_ptr<ResidentPlan>> plans(act.size());
     for (int attempt = 0; attempt < 2; ++attempt) {
         int64_t blocks = 0;
         bool many = false;
-        for (int k : act) {
-            Slot &s = slots[(size_t)k];
-            const int most = act.size() == 1
-                                 ? res_units
-                                 : (int)std::min<double>(
-                                       res_units, (double)need(s) + load(s) / total * (double)spare);
-            if (s.res_tried == 0 || (attempt && s.res_tried != most)) {
-                int rc = build_resident(k, most);
-                if (rc) return rc;
+        double us = 0;
+        uint32_t lds = 0;
+        res_threads = 256;
+        for (size_t i = 0; i < act.size(); ++i) {
+            Slot &s = slots[(size_t)act[i]];
+            const int most = alone ? res_units
+                                   : (int)std::min<double>(res_units, (double)need(s) +
+                                                               load(s) / total * (double)spare);
+            std::shared_ptr<ResidentPlan> &pl = plans[i];
+            if (!attempt && s.res && !wider) pl = s.res;
+            if (!pl || (attempt && pl->most != most)) {
+                if (s.res_none >= most) return unused();
+                pl = plan_team(act[i], most);
+                if (!pl) {
+                    s.res_none = most;
+                    return unused();
+                }
             }
-            if (!s.res) return CFR_OK;
-            if (act.size() == 1) {
-                // the launches of a game alone: about 36 us for the chain,
-                // its streams at 5 TB/s and its sweeps' bytes at 4 TB/s
-                double us = 36.0 + (s.n_seq[0] + s.n_seq[1]) * 60.0 / 4e6;
-                for (int w = 0; w < 2; ++w) us += it.bytes[w] / 5e6;
-                if (s.res->cost_us > us) return CFR_OK;
-            }
-            blocks += s.res->blocks;
-            many = many || s.res->blocks > 1;
+            blocks += pl->blocks;
+            many = many || pl->blocks > 1;
+            us = std::max(us, pl->cost_us);
+            lds = std::max(lds, pl->lds);
+            if (pl->n_seq > kResFewSeq) res_threads = kResThreadsMax;
         }
+        if (many) res_threads = kResThreadsMax;
+        // The launches that it replaces: 36 us for a game alone or 55 for a
+        // batch's chain (58 to 73 us an iteration measured for 2 to 12 games,
+        // 38 to 53 in teams), its streams at 5 TB/s and its sweeps' bytes at 4.
+        double launches = (alone ? 36.0 : 55.0) + seqs * 60.0 / 4e6;
+        for (int w = 0; w < 2; ++w) launches += it.bytes[w] / 5e6;
+        // teams without barriers may take turns
+        const uint32_t room = kResLds / (lds + (uint32_t)res_threads / 64 * kResStage);
+        const double held = (double)res_units * std::min<uint32_t>(room, 2048u / (uint32_t)res_threads);
+        if (us * (many ? 1.0 : std::ceil((double)blocks / held)) > launches) continue;
         // teams with barriers have to be resident all together, one
         // workgroup per compute unit
         if (many && blocks > res_units) continue;
         // workgroup i runs on XCD i % 8: teams of at most 32 on one XCD
         const size_t lane_units = (size_t)std::max(1, res_units / kResXcds);
         std::vector<int> order(act);
+        for (size_t i = 0; i < act.size(); ++i)
+            if (!plans[i]->dev) {
+                if (plans[i] != slots[(size_t)act[i]].res && slots[(size_t)act[i]].res)
+                    (void)hipStreamSynchronize(st);  // launches may still read the old one
+                const int rc = fill_team(act[i], plans[i]);
+                if (rc) return rc;
+                if (!plans[i]->dev) return unused();  // no memory for it
+            }
         std::stable_sort(order.begin(), order.end(), [&](int a, int b) {
             return slots[(size_t)a].res->blocks > slots[(size_t)b].res->blocks;
         });
         std::vector<ResTeam> teams;
         std::vector<int32_t> lane[kResXcds];
-        res_lds = 0;
-        res_threads = many ? kResThreadsMax : 256;
+        res_lds = lds;
         for (int k : order) {
             const ResidentPlan &pl = *slots[(size_t)k].res;
             const int32_t t = (int32_t)teams.size();
             teams.push_back(pl.team);
-            res_lds = std::max(res_lds, pl.lds);
-            if (pl.n_seq > kResFewSeq) res_threads = kResThreadsMax;
             int x = 0;
             for (int i = 1; i < kResXcds; ++i)
                 if (lane[i].size() < lane[x].size()) x = i;
@@ -2364,7 +2405,7 @@ int Engine::setup_resident(const std::vector<int> &act)
         }
         size_t depth = 0;
         for (auto &l : lane) depth = std::max(depth, l.size());
-        if (many && depth > lane_units) return CFR_OK;  // (the whole grid has to fit)
+        if (many && depth > lane_units) return unused();  // (the whole grid has to fit)
         std::vector<int32_t> map(depth * kResXcds, -1);
         for (int x = 0; x < kResXcds; ++x)
             for (size_t i = 0; i < lane[x].size(); ++i) map[i * kResXcds + (size_t)x] = lane[x][i];
@@ -2377,7 +2418,7 @@ int Engine::setup_resident(const std::vector<int> &act)
             void *p = nullptr;
             if (hipMalloc(&p, need) != hipSuccess) {
                 (void)hipGetLastError();
-                return CFR_OK;
+                return unused();
             }
             res_dev = (char *)p;
             res_dev_bytes = need;
@@ -2393,7 +2434,7 @@ int Engine::setup_resident(const std::vector<int> &act)
         resident = 1;
         return CFR_OK;
     }
-    return CFR_OK;
+    return unused();
 }
 
 bool Engine::capturing() const
@@ -2421,18 +2462,21 @@ int Engine::iterate(int64_t n)
     hipError_t e = hipSuccess;
     // (a set-up allocates and waits, which would end a capture)
     if (n >= kResMinIterations && !timing && !capturing()) {
-        if (resident < 0) {
+        // a batch's last game gets the compute units that the others had
+        const Slot &first = slots[(size_t)act[0]];
+        const bool wider = act.size() == 1 && resident == 1 && first.res->most < res_units;
+        if (resident < 0 || wider) {
             // planning, the streams' copy and their memory are paid once: by
             // as many iterations as they save
             res_asked += (double)n;
-            double save = 0, cost = 0;
+            const double save = wider ? kResWiderUs : kResSaveUs;
+            double cost = 0;
             for (int k : act) {
                 const Slot &s = slots[(size_t)k];
-                save += kResSaveUs / (double)act.size();
-                cost += s.res ? 0.0 : kResSetupUs + kResSetupSeqUs * (s.n_seq[0] + s.n_seq[1]);
+                if (!s.res || wider) cost += kResSetupUs + kResSetupSeqUs * (s.n_seq[0] + s.n_seq[1]);
             }
             if (res_asked * save >= cost) {
-                int rc = setup_resident(act);
+                int rc = setup_resident(act, wider);
                 if (rc) return rc;
             }
         }

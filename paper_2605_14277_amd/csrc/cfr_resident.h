@@ -44,6 +44,9 @@ constexpr int64_t kResSeqMax = 1200000;   // sequences of a game at most (its st
 // for 92, 2 ms for 6,300 and 18 ms for 432,000 sequences), and an iteration
 // of it saves 15 us or more over one launch a step.
 constexpr double kResSetupUs = 400, kResSetupSeqUs = 0.04, kResSaveUs = 15;
+// A batch's last game saves 2 to 12 us an iteration in a team of all units
+// (27 instead of 39, 38 instead of 41, 50 instead of 53).
+constexpr double kResWiderUs = 5;
 constexpr int64_t kResMinIterations = 4;  // a shorter run's set-up and copies cost what it saves
 constexpr int64_t kResLaunchIterations = 1024;  // bounds the time of one launch
 
@@ -173,6 +176,7 @@ struct ResRows {
 };
 
 struct ResidentPlan {
+    int most = 0;       // workgroups it was allowed
     int blocks = 0;
     uint32_t lds = 0;   // bytes of the largest workgroup's arrays (without the waves' staging)
     int32_t n_seq = 0;  // of both players
@@ -192,6 +196,14 @@ struct ResidentPlan {
     size_t dev_bytes = 0;
     ResTeam team;
 };
+
+// Workgroups that a game of n sequences needs at least (what every one keeps of
+// its sequences fills its LDS).
+inline int64_t res_least_blocks(int64_t n, int prec)
+{
+    const int64_t bytes = n * (int64_t)(accum_bytes(prec) + 2 * value_bytes(prec) + 10);
+    return (bytes + kResLds - 1) / kResLds;
+}
 
 // Chooses a team size (at most max_blocks) and cuts for a game, or returns
 // false when its state fits no team's LDS.  seq_base: the game's first

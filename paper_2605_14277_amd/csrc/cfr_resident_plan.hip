@@ -118,8 +118,7 @@ bool plan_resident(const ResSource &src, const ResRows rows[2], const int64_t se
     static const int kSizes[] = {256, 192, 128, 96, 64, 48, 32, 24, 16, 12, 8, 4, 2, 1};
     for (int blocks : kSizes) {
         if (blocks > std::min(max_blocks, kResCus)) continue;
-        const double state = (double)(n_seq[0] + n_seq[1]) * (R + 2 * V + 10);
-        if (state > (double)blocks * kResLds) continue;
+        if (res_least_blocks((int64_t)n_seq[0] + n_seq[1], prec) > blocks) continue;
         if (total / blocks + 2 * barrier_us(blocks) > best + 2.0) continue;
         const bool lean = blocks > 1;
         const double per_seq = R + 2 * V + 12 + (lean ? 0 : R + V);
