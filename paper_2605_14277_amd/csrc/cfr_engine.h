@@ -172,6 +172,13 @@ struct RangeAlloc {
 // KiB of doubles stay in the host's caches while the next part arrives).
 constexpr size_t kExportHead = 256;
 constexpr int32_t kExportPart = 1 << 16;
+// It is allocated once, for the longest vector (20 to 270 us, 70 mostly): at
+// once for a vector of kExportNow sequences, which saves that much (100,000:
+// 207 us plain, 50 staged), else after kExportPlain plain copies, which lose
+// as much between them (45 to 65 us each for up to 13,000 sequences, 21 to 27
+// staged): a new solver of a small game is read once at no cost.
+constexpr int32_t kExportNow = 1 << 15;
+constexpr int kExportPlain = 4;
 static_assert(sizeof(Scalars) <= kExportHead && sizeof(Scalars) % 8 == 0, "export head");
 
 // Stream form 3 of one product: a derived copy of every game's matrix in
@@ -330,10 +337,11 @@ struct Engine {
     bool pending = false;
     std::vector<int> pending_set;
     Scalars *eval_stage = nullptr;
-    // Page-locked staging of fetch_vector, made by the first one: a game's
+    // Page-locked staging of fetch_vector, made once (export_ready): a game's
     // scalars, then two parts of exp_part sequences each.
     char *exp_stage = nullptr;
     int32_t exp_part = 0;
+    int exp_plain = 0;  // vectors copied plainly before it was made
     hipEvent_t exp_ev[2] = {nullptr, nullptr};
     hipEvent_t eval_ev = nullptr;
 

@@ -2770,21 +2770,20 @@ int Engine::time_spmv(int which, int reps, double *ms)
     return CFR_OK;
 }
 
-// Room for parts of n sequences (at most kExportPart); false: use plain copies.
+// The staging for a vector of n sequences; false: use plain copies.
 bool Engine::export_ready(int32_t n)
 {
     if (no_alloc || capturing()) return false;
+    if (exp_stage) return true;
+    if (n < kExportNow && exp_plain < kExportPlain) return false;
     for (hipEvent_t &ev_ : exp_ev)
         if (!ev_ && hipEventCreateWithFlags(&ev_, hipEventDisableTiming) != hipSuccess) {
             ev_ = nullptr;
             (void)hipGetLastError();
             return false;
         }
-    const int32_t part = std::min(n, kExportPart);
-    if (part <= exp_part) return true;
-    if (exp_stage) (void)hipHostFree(exp_stage);  // nothing is in flight between fetches
-    exp_stage = nullptr;
-    exp_part = 0;
+    // room for the longest vector that any game here can have
+    const int32_t part = (int32_t)std::min<int64_t>(std::max(cap.seq[0], cap.seq[1]), kExportPart);
     void *p = nullptr;
     if (hipHostMalloc(&p, kExportHead + 2 * sizeof(double) * (size_t)part, hipHostMallocDefault) !=
             hipSuccess ||
@@ -2860,6 +2859,7 @@ int Engine::fetch_vector(int k, int player, int what, double *out)
     if (!rc) rc = check_mark(hs);
     if (rc) return rc;
     if (what == 1 && hs.W <= 0) return fetch_vector(k, player, 0, out);  // no iteration yet
+    ++exp_plain;
     for (int32_t i = 0; i < n; ++i) {
         double v;
         if (el == 8) {
