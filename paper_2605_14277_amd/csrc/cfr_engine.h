@@ -372,7 +372,8 @@ struct Engine {
     int res_grid = 0;
     uint32_t res_lds = 0;
     int res_threads = 0;
-    double res_asked = 0;  // iterations asked for while the loop was not set up
+    double res_asked = 0;  // iterations asked for since the last set-up, without one
+    int res_vain = 0;      // set-ups since one was used
     bool res_coop = false;
     int64_t res_launches = 0, res_setups = 0, exp_allocs = 0;  // for reports
 

@@ -2473,11 +2473,13 @@ int Engine::iterate(int64_t n)
             double cost = 0;
             for (int k : act) {
                 const Slot &s = slots[(size_t)k];
-                if (!s.res || wider) cost += kResSetupUs + kResSetupSeqUs * (s.n_seq[0] + s.n_seq[1]);
+                if (!s.res || wider) cost += res_setup_us((int64_t)s.n_seq[0] + s.n_seq[1]);
             }
-            if (res_asked * save >= cost) {
+            if (res_asked * save >= std::ldexp(cost, res_vain)) {
                 int rc = setup_resident(act, wider);
                 if (rc) return rc;
+                res_asked = 0;
+                res_vain = resident == 1 ? 0 : std::min(res_vain + 1, kResBackoff);
             }
         }
         if (resident == 1) {

@@ -40,10 +40,21 @@ constexpr uint32_t kResLds = 156 * 1024;  // LDS one workgroup may take
 constexpr int kResBarWords = 1024;        // counters of one team (u32)
 constexpr int kResTeamsMax = 32767;       // games in one launch
 constexpr int64_t kResSeqMax = 1200000;   // sequences of a game at most (its state's bytes decide)
-// Setting a game up takes about 0.4 ms and 40 ns a sequence (measured 0.4 ms
-// for 92, 2 ms for 6,300 and 18 ms for 432,000 sequences), and an iteration
-// of it saves 15 us or more over one launch a step.
-constexpr double kResSetupUs = 400, kResSetupSeqUs = 0.04, kResSaveUs = 15;
+// Setting a game up (us), measured for n sequences of both players: 0.2 to 0.3
+// ms for 92, 0.4 for 458 and 1,500, 0.9 for 2,300, 1.7 for 6,200, 2.6 to 4.7
+// for 17,000, 3.2 to 6.8 for 24,000, 3.0 for 62,000, 2.1 to 5.7 for 113,000, 3.5
+// to 4.8 for 187,000, 5.2 for 315,000 and 11 for 597,000: larger games have
+// fewer team sizes to choose from.  It is done once the iterations asked for
+// since the last set-up would have saved as much; an iteration saves 15 us or
+// more over one launch a step.
+constexpr double kResSaveUs = 15;
+inline double res_setup_us(int64_t n)
+{
+    return 250.0 + 0.25 * (double)(n < 16000 ? n : 16000) + 0.012 * (double)n;
+}
+// A set of games whose teams were not used after all costs twice as much the
+// next time, up to this many times over.
+constexpr int kResBackoff = 10;
 // A batch's last game saves 2 to 12 us an iteration in a team of all units
 // (27 instead of 39, 38 instead of 41, 50 instead of 53).
 constexpr double kResWiderUs = 5;

@@ -71,14 +71,14 @@ def test_games_that_do_not_fit_together(cfr):
     w = Pair(cfr, games, "fp32")
     for g in games:
         w.add(g, max_iterations=0)
-    for _ in range(5):
+    for _ in range(10):
         w.run(1000)
     r = w.stats()
     assert r["state"] == 0 and r["setups"] == 0 and r["device_bytes"] == 0
     # two leave: ten teams fit
     w.remove(w.ids[7])
     w.remove(w.ids[3])
-    for _ in range(5):
+    for _ in range(10):
         w.run(1000)
     r = w.stats()
     print(r, flush=True)
@@ -88,7 +88,7 @@ def test_games_that_do_not_fit_together(cfr):
     w.add(games[3], variant="pcfr+")
     w.add(games[7], variant="cfr+", max_iterations=100)
     w.run(20)
-    for _ in range(5):
+    for _ in range(10):
         w.run(1000)
     r = w.stats()  # one of them stopped at 100
     assert r["state"] in (0, 1) and (r["state"] == 1 or r["teams"] == 0)
@@ -96,7 +96,7 @@ def test_games_that_do_not_fit_together(cfr):
     few = r["blocks"]
     for i in w.ids[1:]:
         w.remove(i)
-    for _ in range(5):
+    for _ in range(10):
         w.run(1000)
     r = w.stats()
     print(r, few, flush=True)
@@ -109,7 +109,7 @@ def test_a_game_without_a_plan_in_its_share_gets_one_later(cfr):
     w = Pair(cfr, games, "fp64")
     for g in games:
         w.add(g, "cfr+")
-    for _ in range(3):
+    for _ in range(4):
         w.run(1000)
     assert w.stats()["state"] == 0 and w.stats()["device_bytes"] == 0
     for i in w.ids[1:]:
