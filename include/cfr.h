@@ -282,9 +282,10 @@ int cfr_kernel_stats(cfr_solver *s, int kernel, int64_t *launches, double *total
  * [9] each player's levels that all of them hold, [10] 1 when its averages
  * stay in device memory, [11], [12] 1 when that product reads quads, [13]
  * the estimate of one iteration (ns); [14] the most workgroups that the
- * device and the stream's compute-unit mask allow one game.  For reports;
- * does not wait.                                                           */
-#define CFR_RESIDENT_STATS 15
+ * device and the stream's compute-unit mask allow one game; [15], [16] ns
+ * of an iteration by launches and inside one, where both were timed (0: the
+ * estimates were clear).  For reports; does not wait.                      */
+#define CFR_RESIDENT_STATS 17
 int cfr_resident_stats(cfr_solver *s, int64_t *out);
 
 /* Checkpointing.  The state of a solver — iteration counter, averaging

@@ -298,7 +298,7 @@ def cfr_kernel_stats(h, kernel: int):
 
 RESIDENT_STATS = ("state", "launches", "teams", "workgroups", "setups", "device_bytes",
                   "stagings", "blocks", "cut0", "cut1", "lean", "quads0", "quads1", "cost_ns",
-                  "units")
+                  "units", "launches_ns", "loop_ns")
 
 
 def _resident_dict(out) -> dict:

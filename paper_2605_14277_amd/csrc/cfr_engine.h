@@ -374,6 +374,11 @@ struct Engine {
     int res_threads = 0;
     double res_asked = 0;  // iterations asked for since the last set-up, without one
     int res_vain = 0;      // set-ups since one was used
+    // Timing of the loop against the launches: -1 none to do, 0 the launches
+    // are next, 1 the loop is
+    int res_trial = -1;
+    bool no_wait = false;  // (not by a call that may not wait)
+    double res_us[2] = {0, 0};  // what they measured, an iteration
     bool res_coop = false;
     int64_t res_launches = 0, res_setups = 0, exp_allocs = 0;  // for reports
 
@@ -454,6 +459,12 @@ struct Engine {
     std::shared_ptr<ResidentPlan> plan_team(int slot, int most);
     int fill_team(int slot, const std::shared_ptr<ResidentPlan> &plan);
     void drop_resident(Slot &s);
+    // n iterations in the loop (n > 0 afterwards: refused) or by launches, and
+    // some by both in turn to see which is faster.  n: iterations left.
+    int run_resident(const std::vector<int> &act, int64_t &n);
+    int run_launches(const std::vector<int> &act, int64_t &n);
+    int try_resident(const std::vector<int> &act, int64_t &n);
+    void drop_teams(const std::vector<int> &set);
     // The failure mark of a game's scalars, as copied back.
     int check_mark(const Scalars &h);
     // What cfr_resident_stats reports, game `slot`'s own entries with it.

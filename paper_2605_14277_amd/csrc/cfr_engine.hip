@@ -2288,7 +2288,8 @@ void Engine::resident_stats(int k, int64_t *out) const
         resident, res_launches, teams, blocks, res_setups, bytes, exp_allocs,
         pl ? pl->blocks : 0, pl ? pl->sh[0].c : 0, pl ? pl->sh[1].c : 0, pl ? pl->team.lean : 0,
         pl ? pl->team.quads[0] : 0, pl ? pl->team.quads[1] : 0,
-        pl ? (int64_t)(1e3 * pl->cost_us) : 0, res_units};
+        pl ? (int64_t)(1e3 * pl->cost_us) : 0, res_units, (int64_t)(1e3 * res_us[0]),
+        (int64_t)(1e3 * res_us[1])};
     std::copy(v, v + CFR_RESIDENT_STATS, out);
 }
 
@@ -2296,13 +2297,11 @@ int Engine::setup_resident(const std::vector<int> &act, bool wider)
 {
     // plans that stay unused are not kept: they hold copies of the streams
     auto unused = [&] {
-        bool any = false;
-        for (int k : act) any = any || slots[(size_t)k].res;
-        if (any) (void)hipStreamSynchronize(st);  // launches may still read them
-        for (int k : act) slots[(size_t)k].res.reset();
+        drop_teams(act);
         return CFR_OK;
     };
     resident = 0;
+    res_trial = -1;
     if (no_alloc || res_refused || !use_graph || async_admission || down_pass != CFR_DOWN_DEFAULT ||
         up_pass != CFR_UP_DEFAULT || act.empty() || act.size() > (size_t)kResTeamsMax)
         return unused();
@@ -2366,7 +2365,12 @@ int Engine::setup_resident(const std::vector<int> &act, bool wider)
         // teams without barriers may take turns
         const uint32_t room = kResLds / (lds + (uint32_t)res_threads / 64 * kResStage);
         const double held = (double)res_units * std::min<uint32_t>(room, 2048u / (uint32_t)res_threads);
-        if (us * (many ? 1.0 : std::ceil((double)blocks / held)) > launches) continue;
+        us *= many ? 1.0 : std::ceil((double)blocks / held);
+        if (us > launches) continue;
+        if (us > kResSure * launches) {
+            res_trial = 0;
+            res_us[0] = res_us[1] = 0;
+        }
         // teams with barriers have to be resident all together, one
         // workgroup per compute unit
         if (many && blocks > res_units) continue;
@@ -2459,7 +2463,6 @@ int Engine::iterate(int64_t n)
     for (int k : act)
         if (slots[(size_t)k].gp.variant < CFR_VANILLA)
             return fail(CFR_ESTATE, "a game has no regret minimiser set");
-    hipError_t e = hipSuccess;
     // (a set-up allocates and waits, which would end a capture)
     if (n >= kResMinIterations && !timing && !capturing()) {
         // a batch's last game gets the compute units that the others had
@@ -2482,29 +2485,49 @@ int Engine::iterate(int64_t n)
                 res_vain = resident == 1 ? 0 : std::min(res_vain + 1, kResBackoff);
             }
         }
+        if (resident == 1 && res_trial >= 0 && !no_wait) {
+            const int rc = try_resident(act, n);
+            if (rc) return rc;
+        }
         if (resident == 1) {
-            HostTimer timer(&host_s[kHostEnqueue], &host_n[kHostEnqueue]);
-            int64_t i = 0;
-            for (; i < n; i += kResLaunchIterations) {
-                e = launch_resident(prec, res_teams, res_map, res_grid, res_lds, res_threads, res_coop,
-                                    (int)std::min<int64_t>(kResLaunchIterations, n - i), mode, sc,
-                                    dp[0], dp[1], st);
-                if (e != hipSuccess) break;
-                ++res_launches;
-            }
-            if (e != hipSuccess && i > 0) return device_error("iteration launch", e);
-            if (e == hipSuccess) {
-                res_ran = true;
-                for (int k : act) slots[(size_t)k].t += n;
-                return CFR_OK;
-            }
-            // refused before anything ran: a launch per step, from here on
-            (void)hipGetLastError();
-            e = hipSuccess;
-            res_refused = true;
-            resident = 0;
+            const int rc = run_resident(act, n);
+            if (rc) return rc;
         }
     }
+    return run_launches(act, n);
+}
+
+int Engine::run_resident(const std::vector<int> &act, int64_t &n)
+{
+    if (n <= 0) return CFR_OK;
+    HostTimer timer(&host_s[kHostEnqueue], &host_n[kHostEnqueue]);
+    hipError_t e = hipSuccess;
+    int64_t i = 0;
+    for (; i < n; i += kResLaunchIterations) {
+        e = launch_resident(prec, res_teams, res_map, res_grid, res_lds, res_threads, res_coop,
+                            (int)std::min<int64_t>(kResLaunchIterations, n - i), mode, sc, dp[0],
+                            dp[1], st);
+        if (e != hipSuccess) break;
+        ++res_launches;
+    }
+    if (e != hipSuccess && i == 0) {
+        // refused before anything ran: a launch per step, from here on
+        (void)hipGetLastError();
+        res_refused = true;
+        resident = 0;
+        return CFR_OK;
+    }
+    if (e != hipSuccess) return device_error("iteration launch", e);
+    res_ran = true;
+    for (int k : act) slots[(size_t)k].t += n;
+    n = 0;
+    return CFR_OK;
+}
+
+int Engine::run_launches(const std::vector<int> &act, int64_t &n)
+{
+    if (n <= 0) return CFR_OK;
+    hipError_t e = hipSuccess;
     // Capturing and instantiating the iteration's graph costs about as much
     // host time as launching twenty iterations directly.  A batch's set of
     // games often changes at every check, so the first short run after a
@@ -2512,26 +2535,77 @@ int Engine::iterate(int64_t n)
     // set runs again (or for a long run).  A lone solver's set never
     // changes: it captures at once.
     constexpr int64_t kGraphNow = 32;
-    if (use_graph && !timing && !gexec && !lone && n < kGraphNow && direct_runs == 0) {
-        ++direct_runs;
-        HostTimer timer(&host_s[kHostEnqueue], &host_n[kHostEnqueue]);
-        for (int64_t i = 0; i < n && e == hipSuccess; ++i) e = enqueue_iteration(st);
-    } else if (use_graph && !timing) {
-        if (!gexec) {
-            e = build_graph();
-            if (e != hipSuccess) {
-                drop_graph();
-                return device_error("graph capture of one iteration", e);
-            }
+    const bool direct = !use_graph || timing || (!gexec && !lone && n < kGraphNow && direct_runs == 0);
+    if (!direct && !gexec) {
+        e = build_graph();
+        if (e != hipSuccess) {
+            drop_graph();
+            return device_error("graph capture of one iteration", e);
         }
+    }
+    if (direct && use_graph && !timing) ++direct_runs;
+    {
         HostTimer timer(&host_s[kHostEnqueue], &host_n[kHostEnqueue]);
-        for (int64_t i = 0; i < n && e == hipSuccess; ++i) e = hipGraphLaunch(gexec, st);
-    } else {
-        for (int64_t i = 0; i < n && e == hipSuccess; ++i) e = enqueue_iteration(st);
+        for (int64_t i = 0; i < n && e == hipSuccess; ++i)
+            e = direct ? enqueue_iteration(st) : hipGraphLaunch(gexec, st);
     }
     if (e != hipSuccess) return device_error("iteration launch", e);
     for (int k : act) slots[(size_t)k].t += n;
+    n = 0;
     return CFR_OK;
+}
+
+// What bounds a large game in the loop (its gathers past the caches, rows that
+// one lane sums in double) and out of it (a chain of 42 to 150 us) is known too
+// roughly for the estimates to decide between them: 2.3e6 to 1.3e7 nonzeros in
+// FP64 measured 1.05 to 2.8 times the loop's estimate and 1.2 to 2.4 times the
+// launches', and six of nineteen games were up to 1.3 times slower in the loop.
+// So both are timed, on iterations that are due anyway; the results are the
+// same bit for bit either way.  By the host's clock: an event recorded behind
+// graph launches has been stamped up to 5 ms early here.
+int Engine::try_resident(const std::vector<int> &act, int64_t &n)
+{
+    using Clock = std::chrono::steady_clock;
+    auto part = [&](int64_t most, bool loop, double *us) {
+        int64_t k = std::min(n, most), left = k;
+        int rc = us ? sync("iteration timing") : CFR_OK;
+        const Clock::time_point from = Clock::now();
+        if (!rc) rc = loop ? run_resident(act, left) : run_launches(act, left);
+        if (!rc && us) rc = sync("iteration timing");
+        if (us) *us = 1e6 * std::chrono::duration<double>(Clock::now() - from).count() / (double)k;
+        n -= k - left;
+        return rc;
+    };
+    int rc = CFR_OK;
+    if (res_trial == 0) {
+        // (a new solver's first launches load the kernels, and the set-up has
+        // let the device rest)
+        if (n > kResTrial) rc = part(std::min(n / 8, 2 * kResTrial), false, nullptr);
+        if (!rc) rc = part(kResTrial, false, &res_us[0]);
+        res_trial = 1;
+    }
+    if (!rc && res_trial == 1 && n > 0) {
+        if (!res_ran) rc = part(kResMinIterations, true, nullptr);
+        if (!rc && resident == 1 && n > 0) {
+            rc = part(kResTrial, true, &res_us[1]);
+            res_trial = -1;
+            if (!rc && res_us[1] > res_us[0]) {
+                resident = 0;
+                drop_teams(act);
+                if (lone) slots[(size_t)act[0]].res_none = res_units;
+                else res_vain = std::min(res_vain + 1, kResBackoff);
+            }
+        }
+    }
+    return rc;
+}
+
+void Engine::drop_teams(const std::vector<int> &set)
+{
+    bool any = false;
+    for (int k : set) any = any || slots[(size_t)k].res;
+    if (any) (void)hipStreamSynchronize(st);  // launches may still read them
+    for (int k : set) slots[(size_t)k].res.reset();
 }
 
 int Engine::evaluate_launch(const std::vector<int> &set, int kind, Scalars *out)
@@ -2708,7 +2782,9 @@ int Engine::run_begin()
     const std::vector<int> act = active_set();
     if (act.empty()) return CFR_OK;
     const int64_t chunk = check_every - phase;
+    no_wait = true;
     int rc = iterate(chunk);
+    no_wait = false;
     if (rc) return rc;
     phase = 0;
     ++checks;

@@ -52,6 +52,12 @@ inline double res_setup_us(int64_t n)
 {
     return 250.0 + 0.25 * (double)(n < 16000 ? n : 16000) + 0.012 * (double)n;
 }
+// The loop and the launches that it replaces are timed against each other over
+// this many iterations, unless the loop's estimate is below this share of the
+// launches': measured times were at most 2.8 times the loop's estimate and at
+// least 1.2 times the launches'.
+constexpr int64_t kResTrial = 32;
+constexpr double kResSure = 0.45;
 // A set of games whose teams were not used after all costs twice as much the
 // next time, up to this many times over.
 constexpr int kResBackoff = 10;
