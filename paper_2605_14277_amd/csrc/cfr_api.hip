@@ -405,7 +405,7 @@ int create_lone(const cfr_game_desc *game, const cfr_options *opt, void *ws, siz
             gp.beta = opt->dcfr_beta;
             gp.gamma = opt->dcfr_gamma;
             int slot = -1;
-            rc = e.add(hg, img, gp, true, false, &slot);
+            rc = e.add(hg, img, gp, true, false, &slot, &hg);
         }
     } catch (...) {
         s->eng.release();
@@ -1048,7 +1048,7 @@ int cfr_batch_add(cfr_batch *b, const cfr_game_desc *game, const cfr_game_params
         p.target = gp->target_exploitability;
         p.max_it = gp->max_iterations;
         int slot = -1;
-        rc = b->eng.add(hg, img, p, b->eng.phase == 0, false, &slot);
+        rc = b->eng.add(hg, img, p, b->eng.phase == 0, false, &slot, &hg);
         if (rc) return rc;
         *id = b->eng.slots[(size_t)slot].id;
         return CFR_OK;
@@ -1138,9 +1138,9 @@ int cfr_batch_add_prepared(cfr_batch *b, const cfr_prepared *p, const cfr_game_p
         if (e.async_admission) {
             // copies overlap the iterations of the games already running
             const bool idle = e.active_set().empty();
-            rc = e.add(p->hg, p->img, q, e.phase == 0 && idle, true, &slot);
+            rc = e.add(p->hg, p->img, q, e.phase == 0 && idle, true, &slot, nullptr);
         } else {
-            rc = e.add(p->hg, p->img, q, e.phase == 0, false, &slot);
+            rc = e.add(p->hg, p->img, q, e.phase == 0, false, &slot, nullptr);
         }
         if (rc) return rc;
         *id = b->eng.slots[(size_t)slot].id;

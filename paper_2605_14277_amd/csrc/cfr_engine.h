@@ -402,7 +402,7 @@ struct Engine {
     // async: copies on the upload stream without waiting (the game's host
     // arrays must outlive them: a prepared game's do).
     int add(const HostGame &hg, const GameImage &img, const GameParams &gp, bool join_now,
-            bool async, int *slot_out);
+            bool async, int *slot_out, HostGame *own);
     void remove(int slot);
     // Makes the stream wait for the admission copies of these games.
     hipError_t wait_uploads(const std::vector<int> &set);
@@ -451,6 +451,8 @@ struct Engine {
     bool capturing() const;
     // n iterations of every active game (no checks).
     int iterate(int64_t n);
+    // The options allow the resident loop.
+    bool may_be_resident() const;
     // Decides on the resident loop for the iterating games and sets up its
     // teams (kept with the games while they are used).
     int setup_resident(const std::vector<int> &act, bool wider);

@@ -1416,7 +1416,7 @@ int Engine::set_params(int k, const GameParams &gp)
 }
 
 int Engine::add(const HostGame &hg, const GameImage &img, const GameParams &gp, bool join_now,
-                bool async, int *slot_out)
+                bool async, int *slot_out, HostGame *own)
 {
     HostTimer timer(&host_s[kHostAdd], &host_n[kHostAdd]);
     int k = -1;
@@ -1548,18 +1548,28 @@ int Engine::add(const HostGame &hg, const GameImage &img, const GameParams &gp, 
             s.fuse_list[p] = pl.fuse_list;
         }
     }
-    // the treeplexes for the resident loop, where its state can fit
-    if (!no_alloc && !async && (int64_t)hg.pl[0].n_seq + hg.pl[1].n_seq <= kResSeqMax) {
+    // the treeplexes for the resident loop, where it can be used and the
+    // state can fit (nothing reads the game's plans after this)
+    if (may_be_resident() &&
+        std::max(hg.pl[0].n_levels, hg.pl[1].n_levels) <= kDownAllMaxDepth &&
+        (int64_t)hg.pl[0].n_seq + hg.pl[1].n_seq <= kResSeqMax) {
         s.res_src = std::make_shared<ResSource>();
         for (int p = 0; p < 2; ++p) {
             const PlayerPlan &pl = hg.pl[p];
             ResSource &rs = *s.res_src;
-            rs.inf_first[p] = pl.inf_first;
-            rs.inf_par[p].resize((size_t)pl.n_inf);
-            for (int32_t j = 0; j < pl.n_inf; ++j)
-                rs.inf_par[p][(size_t)j] = pl.seq_par[(size_t)pl.inf_first[(size_t)j]];
-            rs.child_ptr[p] = pl.child_ptr;
-            rs.child_idx[p] = pl.child_idx;
+            if (own) {
+                PlayerPlan &from = own->pl[p];
+                rs.inf_first[p] = std::move(from.inf_first);
+                rs.seq_par[p] = std::move(from.seq_par);
+                rs.child_ptr[p] = std::move(from.child_ptr);
+                rs.child_idx[p] = std::move(from.child_idx);
+            } else {
+                rs.inf_first[p] = pl.inf_first;
+                rs.seq_par[p] = pl.seq_par;
+                rs.child_ptr[p] = pl.child_ptr;
+                rs.child_idx[p] = pl.child_idx;
+            }
+            rs.n_inf[p] = pl.n_inf;
             rs.lvl_inf[p] = pl.lvl_inf;
             rs.lvl_seq[p] = pl.lvl_seq;
         }
@@ -2293,6 +2303,12 @@ void Engine::resident_stats(int k, int64_t *out) const
     std::copy(v, v + CFR_RESIDENT_STATS, out);
 }
 
+bool Engine::may_be_resident() const
+{
+    return !no_alloc && use_graph && !async_admission && down_pass == CFR_DOWN_DEFAULT &&
+           up_pass == CFR_UP_DEFAULT;
+}
+
 int Engine::setup_resident(const std::vector<int> &act, bool wider)
 {
     // plans that stay unused are not kept: they hold copies of the streams
@@ -2302,8 +2318,7 @@ int Engine::setup_resident(const std::vector<int> &act, bool wider)
     };
     resident = 0;
     res_trial = -1;
-    if (no_alloc || res_refused || !use_graph || async_admission || down_pass != CFR_DOWN_DEFAULT ||
-        up_pass != CFR_UP_DEFAULT || act.empty() || act.size() > (size_t)kResTeamsMax)
+    if (!may_be_resident() || res_refused || act.empty() || act.size() > (size_t)kResTeamsMax)
         return unused();
     const bool alone = act.size() == 1;
     // a workgroup's LDS holds some 2,500 sequences
@@ -2314,7 +2329,7 @@ int Engine::setup_resident(const std::vector<int> &act, bool wider)
     bool several = false;
     for (int k : act) {
         const Slot &s = slots[(size_t)k];
-        if (!s.res_src || std::max(s.n_levels[0], s.n_levels[1]) > kDownAllMaxDepth) return unused();
+        if (!s.res_src) return unused();
         const int64_t n = (int64_t)s.n_seq[0] + s.n_seq[1], b = res_least_blocks(n, prec);
         total += load(s);
         seqs += (double)n;

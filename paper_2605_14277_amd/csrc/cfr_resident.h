@@ -181,7 +181,8 @@ __host__ __device__ inline uint32_t res_layout(Shallow sh, Share part, uint32_t 
 
 // The treeplexes of a game in level order, kept on the host for planning.
 struct ResSource {
-    std::vector<int32_t> inf_first[2], inf_par[2], child_ptr[2], child_idx[2];
+    int32_t n_inf[2] = {0, 0};
+    std::vector<int32_t> inf_first[2], seq_par[2], child_ptr[2], child_idx[2];
     std::vector<int32_t> lvl_inf[2], lvl_seq[2];
 };
 

@@ -65,15 +65,18 @@ bool plan_resident(const ResSource &src, const ResRows rows[2], const int64_t se
                    C = (uint32_t)compute_bytes(prec);
     const bool quads[2] = {plan.team.quads[0] != 0, plan.team.quads[1] != 0};
     int32_t n_seq[2], n_inf[2], n_lev[2];
-    std::vector<int32_t> seq_inf[2];
+    std::vector<int32_t> seq_inf[2], inf_par[2];
     std::vector<double> weight[2];  // of the subtree at each decision point (us on one workgroup)
     std::vector<int32_t> below[2];  // sequences of that subtree
     double weight_all[2] = {0, 0};
     for (int p = 0; p < 2; ++p) {
-        n_inf[p] = (int32_t)src.inf_par[p].size();
+        n_inf[p] = src.n_inf[p];
         n_seq[p] = (int32_t)src.child_ptr[p].size() - 1;
         n_lev[p] = (int32_t)src.lvl_inf[p].size() - 1;
         if (n_inf[p] < 1) return false;
+        inf_par[p].resize((size_t)n_inf[p]);
+        for (int32_t j = 0; j < n_inf[p]; ++j)
+            inf_par[p][(size_t)j] = src.seq_par[p][(size_t)src.inf_first[p][(size_t)j]];
         const std::vector<int32_t> &rp = *rows[p].ptr;
         seq_inf[p].assign((size_t)n_seq[p], -1);
         weight[p].assign((size_t)n_inf[p], 0.0);
@@ -92,7 +95,7 @@ bool plan_resident(const ResSource &src, const ResRows rows[2], const int64_t se
             }
         }
         for (int32_t j = n_inf[p] - 1; j >= 0; --j) {
-            const int32_t par = src.inf_par[p][(size_t)j];
+            const int32_t par = inf_par[p][(size_t)j];
             below[p][(size_t)j] += src.inf_first[p][(size_t)j + 1] - src.inf_first[p][(size_t)j];
             if (par > 0) {
                 const size_t up = (size_t)seq_inf[p][(size_t)par];
@@ -166,7 +169,7 @@ bool plan_resident(const ResSource &src, const ResRows rows[2], const int64_t se
         int32_t longest = 0;
         for (int p = 0; p < 2 && fits; ++p) {
             const int c = s.c[p];
-            const std::vector<int32_t> &inf_first = src.inf_first[p], &par = src.inf_par[p];
+            const std::vector<int32_t> &inf_first = src.inf_first[p], &par = inf_par[p];
             const std::vector<int32_t> &cptr = src.child_ptr[p], &cidx = src.child_idx[p];
             const int32_t lo = src.lvl_inf[p][(size_t)c], hi = src.lvl_inf[p][(size_t)c + 1];
             ResShallow &h = plan.sh[p];
