@@ -1292,13 +1292,39 @@ int Engine::ensure_quads(const std::vector<int> &set)
 
 int Engine::ensure_codes()
 {
-    for (int w = 0; w < 2; ++w) {
+    // A product is given up before anything is allocated for it when one block
+    // in a few has too many values: with continuous payoffs all have, and
+    // allocating, finding that out and freeing took 0.5 to 1.5 ms of a new
+    // solver's first step.  (The counts are kept in the evaluation's scratch:
+    // every buffer has 256 bytes at least.)
+    uint32_t *const few = (uint32_t *)partials;
+    uint32_t sample[4] = {0, 0, 0, 0};
+    bool seek = false;
+    hipError_t e = hipSuccess;
+    for (int w = 0; w < 2 && e == hipSuccess; ++w) {
         QuadStore &Q = quad[w];
         if (!lone || no_alloc || vec[w] != 3 || Q.coded >= 0) continue;
         Q.coded = 0;
         const Slot &s = slots[0];
+        if (s.nq[w] < kCodeMinQuads || s.blocks[w].empty()) continue;
+        if (!seek) e = hipMemsetAsync(few, 0, sizeof sample, st);
+        const int32_t every = ((int32_t)s.blocks[w].size() + kCodeSample - 1) / kCodeSample;
+        if (e == hipSuccess)
+            e = launch_quad_code(prec, w == 0 ? it.csr : it.csc, w == 0 ? it.n_csr : it.n_csc, every,
+                                 Q.idx, Q.val, nullptr, nullptr, nullptr, few + 2 * w, st);
+        Q.coded = -1;
+        seek = true;
+    }
+    if (e == hipSuccess && seek) e = hipMemcpyAsync(sample, few, sizeof sample, hipMemcpyDeviceToHost, st);
+    if (e == hipSuccess && seek) e = hipStreamSynchronize(st);
+    if (e != hipSuccess) return device_error("quad codes", e);
+    for (int w = 0; w < 2; ++w) {
+        QuadStore &Q = quad[w];
+        if (!lone || no_alloc || vec[w] != 3 || Q.coded >= 0) continue;
+        Q.coded = 0;
+        if (sample[2 * w]) continue;
+        const Slot &s = slots[0];
         const size_t blocks = s.blocks[w].size(), V = value_bytes(prec);
-        if (s.nq[w] < kCodeMinQuads || blocks == 0) continue;
         size_t at = 8 * (size_t)(s.qb[w] + s.nq[w]);
         auto take = [&at](size_t bytes) {
             at = (at + 255) & ~(size_t)255;
@@ -1321,9 +1347,9 @@ int Engine::ensure_codes()
             Q.code_bytes = at;
         }
         uint32_t status[2] = {0, 0};
-        hipError_t e = hipMemsetAsync(Q.code + o_status, 0, 8, st);
+        e = hipMemsetAsync(Q.code + o_status, 0, 8, st);
         if (e == hipSuccess)
-            e = launch_quad_code(prec, w == 0 ? it.csr : it.csc, w == 0 ? it.n_csr : it.n_csc, Q.idx,
+            e = launch_quad_code(prec, w == 0 ? it.csr : it.csc, w == 0 ? it.n_csr : it.n_csc, 1, Q.idx,
                                  Q.val, Q.code, Q.code + o_dict, (int32_t *)(Q.code + o_count),
                                  (uint32_t *)(Q.code + o_status), st);
         if (e == hipSuccess)

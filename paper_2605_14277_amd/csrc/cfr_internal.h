@@ -276,16 +276,18 @@ hipError_t launch_quad_fill(int prec, const int32_t *ptr, const int32_t *idx, co
 // code: two 32-bit words a quad (aligned group; four codes), dict: kCodes
 // values a block, n_dict: how many of them.  status (two words, zeroed by the
 // caller): [0] some block has too many distinct values, the rest is then
-// unusable; [1] values of all blocks.
+// unusable; [1] values of all blocks.  With code null only [0] is
+// found, from one block in `every` (1 otherwise).
 constexpr int kCodes = 255;
+constexpr int32_t kCodeSample = 256;  // blocks looked at first: one a compute unit
 // Smallest product (quads) whose coded form is sought.  Below it a product is
 // bound by its launch and its load chain (150000 quads: 4.9 us plain, 5.0
 // coded); 490000 take 8.4 us plain and 8.1 coded in FP32_ACC64, 11.0 and 9.1
 // in FP64; 2.0 million 10.5 and 9.2, 18.3 and 13.8.
 constexpr int64_t kCodeMinQuads = 1 << 18;
-hipError_t launch_quad_code(int prec, const SpmvBlock *tab, int32_t n_tab, const uint32_t *qidx,
-                            const void *qval, void *code, void *dict, int32_t *n_dict,
-                            uint32_t *status, hipStream_t st);
+hipError_t launch_quad_code(int prec, const SpmvBlock *tab, int32_t n_tab, int32_t every,
+                            const uint32_t *qidx, const void *qval, void *code, void *dict,
+                            int32_t *n_dict, uint32_t *status, hipStream_t st);
 // launch_spmv over the coded form (same blocks, 8 or 16 nonzeros a thread).
 hipError_t launch_spmv_coded(int prec, int items, const SpmvBlock *tab, int32_t n_tab,
                              const int32_t *ptr, const void *code, const void *dict,

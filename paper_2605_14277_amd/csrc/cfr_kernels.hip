@@ -1999,10 +1999,12 @@ __global__ __launch_bounds__(kThreads) void k_quad_fill(
 // position is looked up.  status[0] is set when some block has more than
 // kCodes of them (its codes are then not written), status[1] counts the
 // values of all blocks.  A value's bits are its key; the empty key is a NaN's,
-// which no payoff has.
+// which no payoff has.  Without code only status[0] is found, from one block
+// in `every`.
 constexpr int kCodeSlots = 1024;
 template <int P>
 __global__ __launch_bounds__(kThreads) void k_quad_code(const SpmvBlock *__restrict__ tab,
+                                                        int32_t every,
                                                         const uint32_t *__restrict__ qidx,
                                                         const typename Types<P>::V *__restrict__ qval,
                                                         uint2 *__restrict__ code,
@@ -2017,7 +2019,7 @@ __global__ __launch_bounds__(kThreads) void k_quad_code(const SpmvBlock *__restr
     __shared__ uint32_t num[kCodeSlots];
     __shared__ uint32_t count, distinct, over;
     const int tid = threadIdx.x;
-    const SpmvBlock bk = tab[blockIdx.x];
+    const SpmvBlock bk = tab[(int32_t)blockIdx.x * every];
     for (int i = tid; i < kCodeSlots; i += kThreads) key[i] = kEmpty;
     if (tid == 0) {
         count = distinct = 0;
@@ -2053,11 +2055,12 @@ __global__ __launch_bounds__(kThreads) void k_quad_code(const SpmvBlock *__restr
     __syncthreads();
     if (over || distinct > (uint32_t)kCodes) {
         if (tid == 0) {
-            n_dict[blockIdx.x] = 0;
+            if (n_dict) n_dict[blockIdx.x] = 0;
             atomicOr(&status[0], 1u);
         }
         return;
     }
+    if (!code) return;
     for (int i = tid; i < kCodeSlots; i += kThreads)
         if (key[i] != kEmpty) {
             const uint32_t c = atomicAdd(&count, 1u);
@@ -2635,21 +2638,23 @@ hipError_t launch_quad_fill(int prec, const int32_t *ptr, const int32_t *idx, co
 }
 
 template <int P>
-hipError_t quad_code_t(const SpmvBlock *tab, int32_t n_tab, const uint32_t *qidx, const void *qval,
-                       void *code, void *dict, int32_t *n_dict, uint32_t *status, hipStream_t st)
+hipError_t quad_code_t(const SpmvBlock *tab, int32_t n_tab, int32_t every, const uint32_t *qidx,
+                       const void *qval, void *code, void *dict, int32_t *n_dict, uint32_t *status,
+                       hipStream_t st)
 {
     using V = typename Types<P>::V;
     if (n_tab <= 0) return hipSuccess;
-    hipLaunchKernelGGL((k_quad_code<P>), dim3((unsigned)n_tab), dim3(kThreads), 0, st, tab, qidx,
-                       (const V *)qval, (uint2 *)code, (V *)dict, n_dict, status);
+    hipLaunchKernelGGL((k_quad_code<P>), dim3((unsigned)((n_tab + every - 1) / every)),
+                       dim3(kThreads), 0, st, tab, every, qidx, (const V *)qval, (uint2 *)code,
+                       (V *)dict, n_dict, status);
     return hipGetLastError();
 }
 
-hipError_t launch_quad_code(int prec, const SpmvBlock *tab, int32_t n_tab, const uint32_t *qidx,
-                            const void *qval, void *code, void *dict, int32_t *n_dict,
-                            uint32_t *status, hipStream_t st)
+hipError_t launch_quad_code(int prec, const SpmvBlock *tab, int32_t n_tab, int32_t every,
+                            const uint32_t *qidx, const void *qval, void *code, void *dict,
+                            int32_t *n_dict, uint32_t *status, hipStream_t st)
 {
-    CFR_DISPATCH(prec, quad_code_t<P>(tab, n_tab, qidx, qval, code, dict, n_dict, status, st));
+    CFR_DISPATCH(prec, quad_code_t<P>(tab, n_tab, every, qidx, qval, code, dict, n_dict, status, st));
 }
 
 template <int P, bool SEQ, int NQ>
