@@ -2687,7 +2687,7 @@ int Engine::evaluate_launch(const std::vector<int> &set, int kind, Scalars *out)
         q.tab = T->up[p];
         q.root = T->root[p];
         // levels from the root down that no game has more than kBrEntries
-        // entries of
+        // entries of, and at most kBrScan entries in all
         while (q.levels < (int)T->up_level[p].size() && q.levels < kBrLevels) {
             bool fits = true;
             for (int k : set) {
@@ -2696,9 +2696,9 @@ int Engine::evaluate_launch(const std::vector<int> &set, int kind, Scalars *out)
                     fits &= s.lvl_inf[p][(size_t)q.levels + 1] - s.lvl_inf[p][(size_t)q.levels] <=
                             kBrEntries * kRangeBlock;
             }
-            if (!fits) break;
-            q.start[q.levels + 1] = q.start[q.levels] + T->up_level[p][(size_t)q.levels].second;
-            ++q.levels;
+            const int32_t end = q.start[q.levels] + T->up_level[p][(size_t)q.levels].second;
+            if (!fits || end > kBrScan) break;
+            q.start[++q.levels] = end;
         }
         for (int L = (int)T->up_level[p].size() - 1; L >= q.levels; --L) {
             const auto &ul = T->up_level[p][(size_t)L];

@@ -223,21 +223,24 @@ hipError_t launch_shallow(int prec, int variant, const DevPlayer &p, double usig
 // xbar = s / W per game (x where W = 0), 1 at each game's empty sequence.
 hipError_t launch_normalize(int prec, const RangeBlock *tab, int32_t n_tab, const DevPlayer &p,
                             const Scalars *sc, hipStream_t st);
-// One level of the best-response max-sweep (values in vinf).
 // Sequences [lo, hi) of one game's vector (x and acc start at the game) as
 // doubles into page-locked memory, and with lo 0 its scalars into head.
 hipError_t launch_export(int prec, const void *x, const void *acc, const Scalars *sc, int what,
                          int32_t lo, int32_t hi, double *out, Scalars *head, hipStream_t st);
+// One level of the best-response max-sweep (values in vinf).
 hipError_t launch_br(int prec, const RangeBlock *tab, int32_t n_tab, const DevPlayer &p,
                      double usign, hipStream_t st);
-// Per game: usign*g[root] + sum of vinf over the root decision points,
-// into sc[slot].out[out_index].
 // The shallow levels of both players' max-sweeps over a set of games, and
 // their values at the empty sequence (Scalars::out[0] and [1]).  tab holds
 // the levels' entries one level after the other, level lv in [start[lv],
-// start[lv + 1]), at most kBrEntries of them a game and level; root one entry
-// a game.
+// start[lv + 1]), at most kBrEntries of them a game and level and kBrScan in
+// all; root one entry a game.
 constexpr int kBrLevels = 24, kBrEntries = 4, kBrThreads = 1024;
+// Every game's workgroups look through all entries for their own, so a level
+// that would make them more is a launch of its own: 8192 games of three levels
+// took 1922 us a check with two iterations without this limit, 1500 with it,
+// 1617 with 8192 entries; 256 games 166 either way, 183 with launches only.
+constexpr int32_t kBrScan = kBrThreads;
 struct BrTail {
     struct Player {
         const RangeBlock *tab;
