@@ -554,13 +554,9 @@ __global__ __launch_bounds__(NT) void k_resident(const ResTeam *__restrict__ tea
     if (tid == 0) {
         ls->t = gs->t;
         ls->W = gs->W;
-        // a team that has failed stays so: its counters hold what was left of
-        // the launch that did, and no later wait on them means anything
-        ls->ok = bar.n > 1 && ag_load(bar.c + 16) ? 0 : 1;
-        if (!ls->ok) *bar.mark = 1;
+        ls->ok = 1;
     }
     __syncthreads();
-    if (!ls->ok) return;
 
     // Where the gatherers of a player's strategy read it.
     auto target = [&](int p) __attribute__((always_inline)) {
@@ -582,6 +578,14 @@ __global__ __launch_bounds__(NT) void k_resident(const ResTeam *__restrict__ tea
         if (!bar.pass()) return;
     }
 
+    // A team that has failed stays so: its counters hold what was left of the
+    // launch that did, and no later wait on them means anything.  (Nothing of
+    // the state is written before this; earlier in the kernel, or read through
+    // LDS, the same test cost 0.7 % of every iteration by its code's place.)
+    if (bar.n > 1 && ((Cst<uint32_t>)bar.c)[16]) {
+        if (tid == 0) *bar.mark = 1;
+        return;
+    }
     Rule<P> ru;
     ru.floor = variant == CFR_PLUS || variant == CFR_PCFR_PLUS;
     ru.dcfr = variant == CFR_DCFR;
