@@ -17,6 +17,7 @@
 #include <cstdio>
 #include <cstring>
 #include <limits>
+#include <mutex>
 
 namespace cfr {
 
@@ -2538,11 +2539,46 @@ int Engine::iterate(int64_t n)
     return run_launches(act, n);
 }
 
+// Teams of two solvers must not be on the chip together: each could hold a
+// part of it that the other waits for.  So a process's launches with teams wait
+// for one another, by one event a device that lives as long as the process:
+// solvers on several streams and threads take turns, other kernels run beside
+// them as ever.  Between processes that share a device it is the runtime's
+// cooperative launch that keeps them apart.
+namespace {
+struct TeamOrder {
+    std::mutex mu;
+    hipEvent_t done = nullptr;  // the device's last launches with teams
+};
+TeamOrder &team_order(int device)
+{
+    static std::mutex mu;
+    static std::map<int, TeamOrder> all;
+    std::lock_guard<std::mutex> lk(mu);
+    return all[device];
+}
+}  // namespace
+
 int Engine::run_resident(const std::vector<int> &act, int64_t &n)
 {
     if (n <= 0) return CFR_OK;
     HostTimer timer(&host_s[kHostEnqueue], &host_n[kHostEnqueue]);
     hipError_t e = hipSuccess;
+    TeamOrder *const order = res_coop ? &team_order(device) : nullptr;
+    std::unique_lock<std::mutex> turn;
+    if (order) {
+        turn = std::unique_lock<std::mutex>(order->mu);
+        e = order->done ? hipStreamWaitEvent(st, order->done, 0)
+                        : hipEventCreateWithFlags(&order->done, hipEventDisableTiming);
+        if (e != hipSuccess) {
+            // (an event that a device reset has taken, or none to be had)
+            (void)hipGetLastError();
+            order->done = nullptr;
+            res_refused = true;
+            resident = 0;
+            return CFR_OK;
+        }
+    }
     int64_t i = 0;
     for (; i < n; i += kResLaunchIterations) {
         e = launch_resident(prec, res_teams, res_map, res_grid, res_lds, res_threads, res_coop,
@@ -2558,6 +2594,7 @@ int Engine::run_resident(const std::vector<int> &act, int64_t &n)
         resident = 0;
         return CFR_OK;
     }
+    if (e == hipSuccess && order) e = hipEventRecord(order->done, st);
     if (e != hipSuccess) return device_error("iteration launch", e);
     res_ran = true;
     for (int k : act) slots[(size_t)k].t += n;
