@@ -174,11 +174,11 @@ constexpr size_t kExportHead = 256;
 constexpr int32_t kExportPart = 1 << 16;
 // It is allocated once, for the longest vector (20 to 270 us, 70 mostly): at
 // once for a vector of kExportNow sequences, which saves that much (100,000:
-// 207 us plain, 50 staged), else after kExportPlain plain copies, which lose
-// as much between them (45 to 65 us each for up to 13,000 sequences, 21 to 27
-// staged): a new solver of a small game is read once at no cost.
+// 207 us plain, 50 staged), else after kExportPlain plain copies (45 to 65 us
+// each for up to 13,000 sequences, 21 to 27 staged): a new solver of a small
+// game is read once, both players, at no cost.
 constexpr int32_t kExportNow = 1 << 15;
-constexpr int kExportPlain = 4;
+constexpr int kExportPlain = 2;
 static_assert(sizeof(Scalars) <= kExportHead && sizeof(Scalars) % 8 == 0, "export head");
 
 // Stream form 3 of one product: a derived copy of every game's matrix in
