@@ -45,9 +45,10 @@ constexpr int64_t kResSeqMax = 1200000;   // sequences of a game at most (its st
 // for 17,000, 3.2 to 6.8 for 24,000, 3.0 for 62,000, 2.1 to 5.7 for 113,000, 3.5
 // to 4.8 for 187,000, 5.2 for 315,000 and 11 for 597,000: larger games have
 // fewer team sizes to choose from.  It is done once the iterations asked for
-// since the last set-up would have saved as much; an iteration saves 15 us or
-// more over one launch a step.
-constexpr double kResSaveUs = 15;
+// since the last set-up would have saved as much; an iteration saves 15 to 70 us
+// over one launch a step (17,000 sequences 38 to 23, 92 26 to 8, 6,300 43 to 18,
+// 118,000 106 to 33).
+constexpr double kResSaveUs = 20;
 inline double res_setup_us(int64_t n)
 {
     return 250.0 + 0.25 * (double)(n < 16000 ? n : 16000) + 0.012 * (double)n;
