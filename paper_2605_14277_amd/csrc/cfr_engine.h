@@ -362,6 +362,7 @@ struct Engine {
     // The resident loop over the iterating games: -1 not decided since their
     // set or tiling changed, 0 not used, 1 its teams are set up.
     int resident = -1;
+    uint64_t serial = 0;       // of this engine in the process (launches with teams)
     int res_units = 1;         // workgroups of a team at most (team_units)
     bool res_refused = false;  // a launch of it was refused: not used again
     bool res_ran = false;  // some launch of it was enqueued (its failure mark is read back)

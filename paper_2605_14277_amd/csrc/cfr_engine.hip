@@ -12,6 +12,7 @@
 #include "cfr_engine.h"
 
 #include <algorithm>
+#include <atomic>
 #include <chrono>
 #include <cmath>
 #include <cstdio>
@@ -931,6 +932,8 @@ int Engine::init(const Capacity &c, int precision, int dev, hipStream_t stream, 
     // value slots are addressed as 4 * sequence in int32
     if (c.seq[0] > (int64_t)1 << 29 || c.seq[1] > (int64_t)1 << 29)
         return fail(CFR_EINVAL, "more than 2^29 sequences per player");
+    static std::atomic<uint64_t> engines{0};
+    serial = ++engines;
     cap = c;
     prec = precision;
     device = dev;
@@ -2548,7 +2551,8 @@ int Engine::iterate(int64_t n)
 namespace {
 struct TeamOrder {
     std::mutex mu;
-    hipEvent_t done = nullptr;  // the device's last launches with teams
+    hipEvent_t done = nullptr;  // the device's last launches with teams,
+    uint64_t whose = 0;         // and the engine whose they were
 };
 TeamOrder &team_order(int device)
 {
@@ -2568,8 +2572,11 @@ int Engine::run_resident(const std::vector<int> &act, int64_t &n)
     std::unique_lock<std::mutex> turn;
     if (order) {
         turn = std::unique_lock<std::mutex>(order->mu);
-        e = order->done ? hipStreamWaitEvent(st, order->done, 0)
-                        : hipEventCreateWithFlags(&order->done, hipEventDisableTiming);
+        // (an engine's own launches are in order on its stream)
+        if (!order->done)
+            e = hipEventCreateWithFlags(&order->done, hipEventDisableTiming);
+        else if (order->whose != serial)
+            e = hipStreamWaitEvent(st, order->done, 0);
         if (e != hipSuccess) {
             // (an event that a device reset has taken, or none to be had)
             (void)hipGetLastError();
@@ -2594,7 +2601,10 @@ int Engine::run_resident(const std::vector<int> &act, int64_t &n)
         resident = 0;
         return CFR_OK;
     }
-    if (e == hipSuccess && order) e = hipEventRecord(order->done, st);
+    if (e == hipSuccess && order) {
+        e = hipEventRecord(order->done, st);
+        order->whose = serial;
+    }
     if (e != hipSuccess) return device_error("iteration launch", e);
     res_ran = true;
     for (int k : act) slots[(size_t)k].t += n;
