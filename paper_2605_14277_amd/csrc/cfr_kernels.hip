@@ -555,10 +555,13 @@ __global__ __launch_bounds__(kSpmvThreads, 8) void k_spmv_quads(CFR_SPMV_PARAMS(
 #undef CFR_SPMV_PARAMS
 
 // Workgroups of k_spmv_coded a compute unit holds: staging every position
-// takes 38 KB of LDS, FP64 without it 78 registers.
-constexpr int coded_blocks_per_cu(int prec, bool seq)
+// takes 38 KB of LDS or, with 8 nonzeros a thread, 22 KB and 102 registers;
+// FP64 without it 78 registers.
+// Rows of a block at most whose sequential sums read four quads ahead.
+constexpr int32_t kLongRows = 64;
+constexpr int coded_blocks_per_cu(int prec, bool seq, int nq)
 {
-    return seq ? 4 : prec == CFR_FP64 ? 6 : 8;
+    return seq ? (nq == 2 ? 5 : 4) : prec == CFR_FP64 ? 6 : 8;
 }
 
 // Stream form 3 with coded values.  Payoffs of a game usually take few
@@ -580,8 +583,13 @@ constexpr int coded_blocks_per_cu(int prec, bool seq)
 // pointers and values under way while one is summed: 73 and 63 us with a
 // workgroup for each block, 34 and 33 in FP64, whose staging leaves four
 // workgroups a compute unit to hide the loads behind.
+// Sequential sums of long rows are a few lanes' chain of LDS reads and adds:
+// with two quads read ahead such games were slower than their plain quads, with
+// four they are not (us, both products; plain, two, four ahead: rows of 513
+// quads 97 + 156, 141 + 252, 68 + 109; of 160 199 + 76, 164 + 80, 101 + 41, by 8
+// nonzeros a thread 237 + 90, 350 + 131, 194 + 69).
 template <int P, bool SEQ, int NQ>
-__global__ __launch_bounds__(kSpmvThreads, coded_blocks_per_cu(P, SEQ)) void k_spmv_coded(
+__global__ __launch_bounds__(kSpmvThreads, coded_blocks_per_cu(P, SEQ, NQ)) void k_spmv_coded(
     int32_t n_blk, const SpmvBlock *__restrict__ tab, const int32_t *__restrict__ ptr,
     const uint2 *__restrict__ code, const typename Types<P>::V *__restrict__ dict,
     const int32_t *__restrict__ n_dict, const typename Types<P>::V *__restrict__ xin,
@@ -708,8 +716,43 @@ __global__ __launch_bounds__(kSpmvThreads, coded_blocks_per_cu(P, SEQ)) void k_s
             if (tid == 0) s_ptr[nr] = per * n;
             __syncthreads();
             if constexpr (SEQ) {
-                // whole quads, the next two on their way while two are added
-                if (tid < nr) {
+                // whole quads, the next ones on their way while some are
+                // added: two at a time of short rows; of long ones, where a
+                // few lanes work and nothing else hides the reads, four
+                if (nr <= kLongRows) {
+                    if (tid < nr) {
+                        int32_t i = s_ptr[tid];
+                        const int32_t z = s_ptr[tid + 1];
+                        C acc = 0;
+                        L u[4][4], t[4][4];
+                        auto get = [&](int32_t at, L(&o)[4][4]) __attribute__((always_inline)) {
+#pragma unroll
+                            for (int q = 0; q < 4; ++q)
+                                load4_lds(&prod[at + 4 * q < z ? at + 4 * q : 0], o[q]);
+                        };
+                        auto add = [&](const L(&o)[4]) __attribute__((always_inline)) {
+#pragma unroll
+                            for (int k = 0; k < 4; ++k) acc = acc + (C)o[k];
+                        };
+                        get(i, u);
+                        for (; i + 32 <= z; i += 32) {
+                            get(i + 16, t);
+#pragma unroll
+                            for (int q = 0; q < 4; ++q) add(u[q]);
+                            get(i + 32, u);
+#pragma unroll
+                            for (int q = 0; q < 4; ++q) add(t[q]);
+                        }
+                        get(i + 16, t);
+#pragma unroll
+                        for (int q = 0; q < 4; ++q)
+                            if (i + 4 * q < z) add(u[q]);
+#pragma unroll
+                        for (int q = 0; q < 4; ++q)
+                            if (i + 16 + 4 * q < z) add(t[q]);
+                        yout[rb + tid] = (V)acc;
+                    }
+                } else if (tid < nr) {
                     int32_t i = s_ptr[tid];
                     const int32_t z = s_ptr[tid + 1];
                     C acc = 0;
@@ -2664,10 +2707,11 @@ hipError_t spmv_coded_launch(const SpmvBlock *tab, int32_t n_tab, const int32_t 
                              hipStream_t st, hipEvent_t ev0, hipEvent_t ev1)
 {
     using V = typename Types<P>::V;
-    // as many workgroups as the 256 compute units hold, with equal shares
-    constexpr int32_t kHeld = 256 * coded_blocks_per_cu(P, SEQ);
-    const int32_t share = (n_tab + kHeld - 1) / kHeld;
-    unsigned grid = (unsigned)((n_tab + share - 1) / share);
+    // As many workgroups as the 256 compute units hold, or one a block where
+    // they would have fewer than two each (2200 blocks of one row of 513 quads,
+    // FP32: 10.2 us by 1100 workgroups of two, 9.0 by 2200).
+    constexpr int32_t kHeld = 256 * coded_blocks_per_cu(P, SEQ, NQ);
+    unsigned grid = (unsigned)(n_tab < 2 * kHeld ? n_tab : kHeld);
     if (xcd_remap) grid = (grid + 7) / 8 * 8;
     if (ev0)
         hipExtLaunchKernelGGL((k_spmv_coded<P, SEQ, NQ>), dim3(grid), dim3(kSpmvThreads), 0, st, ev0,
