@@ -19,6 +19,7 @@
 #include <cstring>
 #include <limits>
 #include <mutex>
+#include <new>
 
 namespace cfr {
 
@@ -2524,7 +2525,14 @@ int Engine::iterate(int64_t n)
                 if (!s.res || wider) cost += res_setup_us((int64_t)s.n_seq[0] + s.n_seq[1]);
             }
             if (res_asked * save >= std::ldexp(cost, res_vain)) {
-                int rc = setup_resident(act, wider);
+                int rc = CFR_OK;
+                try {
+                    rc = setup_resident(act, wider);
+                } catch (const std::bad_alloc &) {
+                    // no host memory for the plans: the iterations need none
+                    resident = 0;
+                    drop_teams(act);
+                }
                 if (rc) return rc;
                 res_asked = 0;
                 res_vain = resident == 1 ? 0 : std::min(res_vain + 1, kResBackoff);
@@ -2870,9 +2878,16 @@ int Engine::run_begin()
     const std::vector<int> act = active_set();
     if (act.empty()) return CFR_OK;
     const int64_t chunk = check_every - phase;
-    no_wait = true;
-    int rc = iterate(chunk);
-    no_wait = false;
+    struct NoWait {
+        bool &on;
+        explicit NoWait(bool &b) : on(b) { on = true; }
+        ~NoWait() { on = false; }
+    };
+    int rc;
+    {
+        NoWait scope(no_wait);
+        rc = iterate(chunk);
+    }
     if (rc) return rc;
     phase = 0;
     ++checks;
