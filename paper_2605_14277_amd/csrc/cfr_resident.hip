@@ -10,11 +10,12 @@
 // cache.  What is left is latency: about 0.6 us for each treeplex level on the
 // way up (a chain of LDS accesses and a division), 1 to 2 us a product of a
 // small game.  One iteration, launch per step against resident: 144 nonzeros
-// 25.7 against 8.3 us; 4.9e4 (double) 42 / 19.8; 1.7e5 38 / 24; 1.3e6 with 9
-// or 10 actions (double) 106 / 34; 3.4e6 (double) 73 / 55; 3.7e6 (float) 90 /
-// 31; 9.7e6 (quads) 110 / 51.  The products of the larger ones run at 4 TB/s:
-// 16 waves a compute unit and the instructions of staging and summing bound
-// them (8 waves: 28 instead of 20 us for both of the 3.4e6 game).
+// 25.7 against 7.6 us; 4.9e4 (double) 42 / 18; 1.7e5 38 / 23; 1.3e6 with 9
+// or 10 actions (double) 106 / 33; 3.4e6 (double) 73 / 54; 3.7e6 (float) 90 /
+// 30; 9.7e6 (quads) 110 / 50.  The products of the larger ones run at 4 TB/s
+// (16 waves a compute unit; 8: 28 instead of 20 us for both of the 3.4e6 game)
+// and wait for their gathers, which fetch as many bytes again as the streams:
+// vector instructions issue in 6 % of the waves' cycles.
 #include "cfr_resident.h"
 
 #include "cfr.h"
