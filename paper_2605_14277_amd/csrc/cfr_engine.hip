@@ -993,7 +993,7 @@ int Engine::init(const Capacity &c, int precision, int dev, hipStream_t stream, 
         e = hipMemsetAsync(dp[p].child_idx, 0, 4 * (size_t)std::max<int64_t>(c.inf[p], 1), st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);
     if (e != hipSuccess) return device_error("workspace initialisation", e);
-    res_units = team_units(device, st);
+    if (!no_alloc) res_units = team_units(device, st);
     // an allocation-free engine admits its one game synchronously on the
     // caller's stream and stages from ordinary host memory
     if (no_alloc) return init_arenas(c);
