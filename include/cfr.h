@@ -161,9 +161,12 @@ typedef struct cfr_options {
                                for games whose iteration state fits the LDS of
                                the compute units, run whole iterations inside
                                one launch (set up once enough iterations have
-                               been asked for to repay it; it keeps a copy of
-                               the payoff streams outside any caller workspace;
-                               same results bit for bit); 0: a launch per step  */
+                               been asked for to repay it, in a call that then
+                               waits for the stream, and timed against the
+                               launches where it is not clearly faster; it keeps
+                               a copy of the payoff streams outside any caller
+                               workspace; same results bit for bit; not while
+                               the stream is captured); 0: a launch per step    */
     int spmv_order;         /* CFR_SPMV_*                                    */
     int down_pass;          /* CFR_DOWN_*                                    */
     int up_pass;            /* CFR_UP_*                                      */
