@@ -224,7 +224,8 @@ int cfr_create(const cfr_game_desc *game, const cfr_options *opt, cfr_solver **o
 int cfr_create_static(const cfr_game_desc *game, const cfr_options *opt, cfr_solver **out);
 
 /* Enqueues n >= 0 iterations on the solver's stream and returns without
- * waiting.  One iteration is Algorithm 2 (ObserveUtility after the payoff
+ * waiting (but the first call, and one that sets up what use_graph names,
+ * wait for the stream).  One iteration is Algorithm 2 (ObserveUtility after the payoff
  * products, then NextStrategy) with the variant's regret update (Algorithms
  * 3-5) and the update schedule of Section 3.5 (alternating: player 1
  * observes A y^t and moves, then player 2 observes -A^T x^{t+1}).  The
