@@ -80,8 +80,6 @@ namespace {
 constexpr int kThreads = 256;
 constexpr int kMaxActs = 8;  // decision points up to this size keep their actions in registers
 
-inline unsigned grid_for(int64_t n) { return (unsigned)((n + kThreads - 1) / kThreads); }
-
 typedef int32_t v4i __attribute__((ext_vector_type(4)));
 typedef float v4f __attribute__((ext_vector_type(4)));
 typedef double v2d __attribute__((ext_vector_type(2)));
