@@ -362,7 +362,7 @@ struct Engine {
     // The resident loop over the iterating games: -1 not decided since their
     // set or tiling changed, 0 not used, 1 its teams are set up.
     int resident = -1;
-    uint64_t serial = 0;       // of this engine in the process (launches with teams)
+    bool in_teams = false;     // counted among the device's streams with teams
     int res_units = 1;         // workgroups of a team at most (team_units)
     bool res_refused = false;  // a launch of it was refused: not used again
     bool res_ran = false;  // some launch of it was enqueued (its failure mark is read back)
@@ -457,6 +457,10 @@ struct Engine {
     // Decides on the resident loop for the iterating games and sets up its
     // teams (kept with the games while they are used).
     int setup_resident(const std::vector<int> &act, bool wider);
+    // This engine's stream among those of the device that launch teams (false:
+    // the other's launches cannot be waited for now).
+    bool join_teams();
+    void leave_teams();
     // A game's plan for at most `most` workgroups (host only; null: none
     // fits), and its device memory (none had: plan->dev stays null).
     std::shared_ptr<ResidentPlan> plan_team(int slot, int most);

@@ -12,7 +12,6 @@
 #include "cfr_engine.h"
 
 #include <algorithm>
-#include <atomic>
 #include <chrono>
 #include <cmath>
 #include <cstdio>
@@ -905,15 +904,41 @@ int64_t RangeAlloc::largest() const
 // Engine
 // ---------------------------------------------------------------------------
 
+// Teams of two solvers must not be on the chip together: each could hold a
+// part of it that the other waits for.  So a process's launches with teams on
+// several streams of a device wait for one another, by one event that lives as
+// long as the process: solvers on several streams and threads take turns, other
+// kernels run beside them as ever.  Launches on one stream are in order, and
+// while only one stream has any the event is left out (5 to 8 us a launch).
+// Between processes that share a device it is the runtime's cooperative launch
+// that keeps them apart.
+namespace {
+struct TeamOrder {
+    std::mutex mu;
+    std::map<hipStream_t, int> streams;  // that launch teams: engines on each
+    hipEvent_t done = nullptr;           // the last launches, while there are several streams,
+    hipStream_t last = nullptr;          // and the stream they are on
+};
+TeamOrder &team_order(int device)
+{
+    static std::mutex mu;
+    static std::map<int, TeamOrder> all;
+    std::lock_guard<std::mutex> lk(mu);
+    return all[device];
+}
+}  // namespace
+
 // Workgroups that a team of the resident loop may have on this device and
 // stream, all of them on the chip at once at one a compute unit: a multiple of
 // eight (they are dealt round over the XCDs).  1 (teams without barriers)
-// where the device launches nothing cooperatively or a compute-unit mask
-// leaves the stream a part of it.
+// where the device launches nothing cooperatively, a compute-unit mask leaves
+// the stream a part of it, or the stream's handle names another one in each
+// thread (their launches could not be told apart).
 static int team_units(int dev, hipStream_t st)
 {
     int units = 0, together = 0;
     uint32_t mask[32] = {};
+    if (st == hipStreamPerThread) return 1;
     // (the named streams 1 and 2 are no handles, and have no mask of their own)
     const hipStream_t of = (uintptr_t)st > 2 ? st : nullptr;
     if (hipDeviceGetAttribute(&units, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
@@ -933,8 +958,6 @@ int Engine::init(const Capacity &c, int precision, int dev, hipStream_t stream, 
     // value slots are addressed as 4 * sequence in int32
     if (c.seq[0] > (int64_t)1 << 29 || c.seq[1] > (int64_t)1 << 29)
         return fail(CFR_EINVAL, "more than 2^29 sequences per player");
-    static std::atomic<uint64_t> engines{0};
-    serial = ++engines;
     cap = c;
     prec = precision;
     device = dev;
@@ -1078,6 +1101,7 @@ void Engine::release()
     if (own_ws && ws) (void)hipFree(ws);
     ws = nullptr;
     for (Slot &s : slots) drop_resident(s);
+    leave_teams();
     if (res_dev) (void)hipFree(res_dev);
     res_dev = nullptr;
     res_dev_bytes = 0;
@@ -2456,6 +2480,7 @@ int Engine::setup_resident(const std::vector<int> &act, bool wider)
         size_t depth = 0;
         for (auto &l : lane) depth = std::max(depth, l.size());
         if (many && depth > lane_units) return unused();  // (the whole grid has to fit)
+        if (many && !join_teams()) return unused();
         std::vector<int32_t> map(depth * kResXcds, -1);
         for (int x = 0; x < kResXcds; ++x)
             for (size_t i = 0; i < lane[x].size(); ++i) map[i * kResXcds + (size_t)x] = lane[x][i];
@@ -2550,26 +2575,37 @@ int Engine::iterate(int64_t n)
     return run_launches(act, n);
 }
 
-// Teams of two solvers must not be on the chip together: each could hold a
-// part of it that the other waits for.  So a process's launches with teams wait
-// for one another, by one event a device that lives as long as the process:
-// solvers on several streams and threads take turns, other kernels run beside
-// them as ever.  Between processes that share a device it is the runtime's
-// cooperative launch that keeps them apart.
-namespace {
-struct TeamOrder {
-    std::mutex mu;
-    hipEvent_t done = nullptr;  // the device's last launches with teams,
-    uint64_t whose = 0;         // and the engine whose they were
-};
-TeamOrder &team_order(int device)
+bool Engine::join_teams()
 {
-    static std::mutex mu;
-    static std::map<int, TeamOrder> all;
-    std::lock_guard<std::mutex> lk(mu);
-    return all[device];
+    if (in_teams) return true;
+    TeamOrder &o = team_order(device);
+    std::lock_guard<std::mutex> lk(o.mu);
+    if (!o.streams.count(st) && o.streams.size() == 1) {
+        // the other stream's launches so far have left no event
+        const hipStream_t other = o.streams.begin()->first;
+        hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+        hipError_t e = o.done ? hipSuccess : hipEventCreateWithFlags(&o.done, hipEventDisableTiming);
+        if (e == hipSuccess) e = hipStreamIsCapturing(other, &cs);
+        if (e == hipSuccess && cs == hipStreamCaptureStatusNone) e = hipEventRecord(o.done, other);
+        if (e != hipSuccess || cs != hipStreamCaptureStatusNone) {
+            (void)hipGetLastError();
+            return false;
+        }
+        o.last = other;
+    }
+    ++o.streams[st];
+    in_teams = true;
+    return true;
 }
-}  // namespace
+
+void Engine::leave_teams()
+{
+    if (!in_teams) return;
+    TeamOrder &o = team_order(device);
+    std::lock_guard<std::mutex> lk(o.mu);
+    if (--o.streams[st] == 0) o.streams.erase(st);
+    in_teams = false;
+}
 
 int Engine::run_resident(const std::vector<int> &act, int64_t &n)
 {
@@ -2578,17 +2614,13 @@ int Engine::run_resident(const std::vector<int> &act, int64_t &n)
     hipError_t e = hipSuccess;
     TeamOrder *const order = res_coop ? &team_order(device) : nullptr;
     std::unique_lock<std::mutex> turn;
+    bool record = false;
     if (order) {
         turn = std::unique_lock<std::mutex>(order->mu);
-        // (an engine's own launches are in order on its stream)
-        if (!order->done)
-            e = hipEventCreateWithFlags(&order->done, hipEventDisableTiming);
-        else if (order->whose != serial)
-            e = hipStreamWaitEvent(st, order->done, 0);
+        record = order->streams.size() > 1;
+        if (record && order->last != st) e = hipStreamWaitEvent(st, order->done, 0);
         if (e != hipSuccess) {
-            // (an event that a device reset has taken, or none to be had)
             (void)hipGetLastError();
-            order->done = nullptr;
             res_refused = true;
             resident = 0;
             return CFR_OK;
@@ -2609,9 +2641,9 @@ int Engine::run_resident(const std::vector<int> &act, int64_t &n)
         resident = 0;
         return CFR_OK;
     }
-    if (e == hipSuccess && order) {
+    if (e == hipSuccess && record) {
         e = hipEventRecord(order->done, st);
-        order->whose = serial;
+        order->last = st;
     }
     if (e != hipSuccess) return device_error("iteration launch", e);
     res_ran = true;

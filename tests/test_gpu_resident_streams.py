@@ -53,3 +53,46 @@ def test_teams_on_several_streams():
     for (name, i), v in got.items():
         for p in range(2):
             assert np.array_equal(v[p], want[name][p]), (name, i, p)
+
+
+def test_streams_that_come_and_go():
+    """One stream with two solvers, then a second and a third stream, without
+    waits between their calls."""
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2605_14277_amd as cfr
+    game, n = GAMES["units"](), 900
+    ref = cfr.Solver(game, use_graph=False)
+    want = {}
+    for done in (n, n + 50, n + 100):
+        ref.step(done - ref.iteration, "cfr+", "alternating")
+        want[done] = [ref.strategy(p, "average") for p in range(2)]
+    ref.close()
+    streams = [torch.cuda.Stream() for _ in range(3)]
+
+    def check(s, done):
+        assert s.resident_stats()["blocks"] > 1
+        for p in range(2):
+            assert np.array_equal(s.strategy(p, "average"), want[done][p])
+
+    a, b = (cfr.Solver(game, stream=streams[0]) for _ in range(2))
+    for s in (a, b):
+        s.step(n, "cfr+", "alternating")
+    c = cfr.Solver(game, stream=streams[1])
+    c.step(n, "cfr+", "alternating")
+    for s in (a, c, b, c, a):  # c 100 more, a 100, b 50
+        s.step(50, "cfr+", "alternating")
+    check(a, n + 100)
+    check(b, n + 50)
+    check(c, n + 100)
+    a.close()
+    b.close()
+    d = cfr.Solver(game, stream=streams[2])
+    for s, k in ((c, 0), (d, n), (d, 50)):
+        s.step(k, "cfr+", "alternating")
+    check(d, n + 50)
+    c.close()
+    d.step(50, "cfr+", "alternating")
+    check(d, n + 100)
+    d.close()
